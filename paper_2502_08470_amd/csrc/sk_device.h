@@ -28,6 +28,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// Lambdas of the sweeps are always inlined: one that is called holds its
+// captures, the kernel arguments with their tables among them, in scratch.
+#define SK_INLINE __attribute__((always_inline))
+
 #define SK_NMAX 12   // largest compiled polynomial order
 #define SK_TMAX 20   // longest interpolation tail (table size)
 #define SK_IFA (2 * SK_NMAX + SK_TMAX + 4)  // 1/m! entries the tail rows index
@@ -65,6 +69,10 @@ __device__ __forceinline__ void sk_st_nt(T* p, T v) { __builtin_nontemporal_stor
 template <typename T>
 __device__ __forceinline__ T sk_ld_nt(const T* p) { return __builtin_nontemporal_load(p); }
 
+// s_waitcnt operand: no vector memory operation in flight (the other counters
+// as they are)
+__host__ __device__ constexpr int sk_waitcnt_vm0() { return 0x0f70; }
+
 // A pointer into LDS (address space 3): its arithmetic is 32-bit, where a
 // generic pointer's would be 64-bit with an unused high half.
 template <typename T> using SkLds = __attribute__((address_space(3))) T*;
@@ -78,6 +86,16 @@ struct SkTab {
                                  // shrink at least by half per row
     R ifa[SK_IFA];               // 1/m!, for rows indexed at run time
 };
+
+// The tables as the cell maps take them: in the kernel's argument segment
+// (constant address space, so that reading them again is never ordered
+// against the kernel's stores).
+#ifdef __HIP_DEVICE_COMPILE__
+#define SK_KARG __attribute__((address_space(4)))
+#else
+#define SK_KARG
+#endif
+template <typename R> using SkTabArg = const SK_KARG SkTab<R>;
 
 // ---------------------------------------------------------------------------
 // compile-time constants
@@ -141,6 +159,10 @@ __device__ __forceinline__ int lane_from_prev_or(int v, int lane0) {
 __device__ __forceinline__ int lane_from_next(int v) {
     return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true);
 }
+// lane r receives the value of lane r+1 and lane 63 its own value of `lane63`
+__device__ __forceinline__ int lane_from_next_or(int v, int lane63) {
+    return __builtin_amdgcn_update_dpp(lane63, v, 0x130, 0xf, 0xf, false);
+}
 
 template <typename R>
 __device__ __forceinline__ R wave_max(R v) {
@@ -200,6 +222,34 @@ template <> struct SkEps<double> { static constexpr double value = 1.0 / (double
 
 __device__ __forceinline__ bool sk_wave_any(bool v) { return __any(v ? 1 : 0) != 0; }
 
+// Cells of small |c| in FP32 (orders N >= 5; of N = 4 they would leave out one
+// row and double the code, which short pairs run through cold).  At a step where every lane of
+// the wave has |c| <= SK_SMALL_C = 2^-6, the terms with a factor c^4 or a
+// higher power are below the rounding of the FP32 state and are not formed: the
+// Toeplitz weights stop at w_3 and the Hankel rows at r = 3 (w_4 <= 2^-28.5, and
+// a row's weight in the edge's values is 1/r! <= 1/24, so an edge moves by less
+// than 2^-32 of its largest coefficient, where its own coefficients are
+// rounded to 2^-24; at the |c| of paths of some hundred steps, ten times
+// smaller, by 2^-45).  The interpolation scheme's cell keeps these rows only
+// while its first tail row, from the same weights, is below half of what the
+// tail rule allows (the terms left out of it are below the other half), so it
+// folds no tail row; otherwise it is computed whole.  The adjoint transposes
+// the same terms.  The test is wave-uniform, once a step (in the pipelined
+// adjoint once a checkpoint segment); the rows it saves are 40% of the
+// multiply-adds of a cell at N = 6.
+#define SK_SMALL_C (1.0 / 64)
+#define SK_SMALL_M 3
+template <typename R, int N>
+constexpr bool sk_small_path() { return sizeof(R) == 4 && N > SK_SMALL_M + 1; }
+// whether every lane's `n` constants allow the small-|c| rows (NaN does not)
+template <int n, typename R>
+__device__ __forceinline__ bool sk_all_small(const R (&c)[n]) {
+    bool big = false;
+#pragma unroll
+    for (int u = 0; u < n; ++u) big = big || !(sk_abs(c[u]) <= (R)SK_SMALL_C);
+    return !sk_wave_any(big);
+}
+
 // ---------------------------------------------------------------------------
 // forward cell map
 // ---------------------------------------------------------------------------
@@ -226,15 +276,21 @@ __device__ __forceinline__ bool sk_wave_any(bool v) { return __any(v ? 1 : 0) !=
 // DS: element stride of DP and DQ (1 for registers; 64 for an LDS array with
 // one slot per lane).
 // Wout (nullable): receives w_m = c^m/m!, m = 1..N (as the rows used them).
+// SMALL: the rows of small |c| (see SK_SMALL_C): SK_SMALL_OFF never,
+// SK_SMALL_ASK where the whole wave allows them (decided here, against
+// small_c), SK_SMALL_ON the caller knows that it does (and of no tail row).
+#define SK_SMALL_OFF 0
+#define SK_SMALL_ASK 1
+#define SK_SMALL_ON 2
 template <typename R, int N, int TMAX, bool WD = false, bool HI = true, bool FIXT = false,
-          int DS = 1>
+          int DS = 1, int SMALL = SK_SMALL_OFF>
 __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N + 1], double P0,
                                             double P1, double Q0, double Q1, R c, bool active,
-                                            const SkTab<R>& tab, R (&Po)[N + 1], R (&Qo)[N + 1],
+                                            SkTabArg<R>& tab, R (&Po)[N + 1], R (&Qo)[N + 1],
                                             double& Po0, double& Po1, double& Qo0, double& Qo1,
                                             R* DP = nullptr, R* DQ = nullptr,
                                             int* Tkept = nullptr, int Tfix = 0,
-                                            R* Wout = nullptr) {
+                                            R* Wout = nullptr, R small_c = (R)SK_SMALL_C) {
     // tail rows unrolled with constant indices (the rest in a loop)
     constexpr int TU = TMAX < SkTailReg<R>::value ? TMAX : SkTailReg<R>::value;
     // rows up to N + TU in the unrolled part (+1 that only decides, when
@@ -252,7 +308,7 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
     // c^m: their Hankel sums are taken against r!/(r+k)!, so that
     // c^r sum_k Q'_k/(r+k)! = w_r sum_k Q'_k r!/(r+k)!, and the tail rows
     // start c^m from w_N N!.
-    auto power = [&](int m) {
+    auto power = [&](int m) SK_INLINE {
         if (!HI && m <= N) {
             w[m] = m == 1 ? c : w[m - 1] * (c * (R)(1.0 / m));
             return;
@@ -261,12 +317,10 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
         cp[m] = cp[m - 1] * c;
         w[m] = HI ? w[m - 1] * (c * (R)(1.0 / m)) : cp[m] * ifact<R>(m);
     };
+    static_assert(!SMALL || sk_small_path<R, N>(), "small-|c| rows: FP32, N >= 4");
+    constexpr int M0 = SMALL != SK_SMALL_OFF ? SK_SMALL_M : MU;
 #pragma unroll
-    for (int m = 1; m <= MU; ++m) power(m);
-    if (Wout) {  // c^m/m!, m = 1..N, for the adjoint of the same cell
-#pragma unroll
-        for (int m = 1; m <= N; ++m) Wout[m - 1] = w[m];
-    }
+    for (int m = 1; m <= M0; ++m) power(m);
     if (WD && !FIXT) {
         // rows 0..N-1 are always written; tail rows only when kept (a replay
         // with the tail length given reads exactly the rows it folds)
@@ -320,14 +374,26 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
         tpp = fma(c, P[0], P[1]);
         tqp = fma(c, Q[0], Q[1]);
     }
-#pragma unroll
-    for (int r = 2; r <= N; ++r) {
+    // row r, 2 <= r <= N, from the weights w_1 .. w_MT
+    auto row = [&](int r, int MT) SK_INLINE {
         // Toeplitz row r, from its k = r term (w_0 = 1)
         R tp = P[r], tq = Q[r];
 #pragma unroll
         for (int k = r - 1; k >= 0; --k) {
+            if (r - k > MT) break;
             tp = fma(w[r - k], P[k], tp);
             tq = fma(w[r - k], Q[k], tq);
+        }
+        if (r > MT) {  // (small |c|: no Hankel part)
+            Po[r] = tp;
+            Qo[r] = tq;
+            if (WD) {
+                DP[(r - 1) * DS] = tpp;
+                DQ[(r - 1) * DS] = tqp;
+                tpp = tp;
+                tqp = tq;
+            }
+            return;
         }
         R hq = (R)0, hp = (R)0;
 #pragma unroll
@@ -349,8 +415,37 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
             tpp = tp;
             tqp = tq;
         }
+    };
+    bool full = true;  // wave-uniform
+    if constexpr (SMALL == SK_SMALL_ON) {
+        static_assert(TMAX == 0, "no tail rows");
+        full = false;
+    } else if constexpr (SMALL == SK_SMALL_ASK) {
+        full = __builtin_amdgcn_ballot_w64(!(sk_abs(c) <= small_c)) != 0 || (TMAX > 0 && FIXT && Tfix > 0);
+        if constexpr (TMAX > 0 && !FIXT) {
+            if (!full) {
+                const R ap = fma(w[1], P[N], fma(w[2], P[N - 1], w[3] * P[N - 2]));
+                const R aq = fma(w[1], Q[N], fma(w[2], Q[N - 1], w[3] * Q[N - 2]));
+                const R lim = (R)(0.5 * SkEps<R>::value) * (sk_abs((R)Po0) + sk_abs((R)Qo0));
+                full = __builtin_amdgcn_ballot_w64(
+                           active && !((R)2 * tab.rmax[0] * (sk_abs(ap) + sk_abs(aq)) <= lim)) != 0;
+            }
+        }
     }
-    if (TMAX > 0) {
+    if (__builtin_expect(full, SMALL == SK_SMALL_OFF)) {
+#pragma unroll
+        for (int m = M0 + 1; m <= MU; ++m) power(m);
+#pragma unroll
+        for (int r = 2; r <= N; ++r) row(r, N);
+    } else {
+#pragma unroll
+        for (int r = 2; r <= N; ++r) row(r, SK_SMALL_M);
+    }
+    if (Wout) {  // c^m/m!, m = 1..N (SMALL: 1..3), for the adjoint of the same cell
+#pragma unroll
+        for (int m = 1; m <= (M0 < N ? M0 : N); ++m) Wout[m - 1] = w[m];
+    }
+    if (TMAX > 0 && __builtin_expect(full, SMALL == SK_SMALL_OFF)) {
         const R scale = (R)SkEps<R>::value * (R)(fabs(Po0) + fabs(Qo0));
         const R ac = sk_abs(c);
         R t0p = (R)0, t0q = (R)0, t1p = (R)0, t1q = (R)0;  // tail into rows 0, 1
@@ -360,7 +455,7 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
         // Tail row t (row r = N + 1 + t) with Toeplitz parts tp, tq and
         // Hankel parts hq, hp: decide whether it is needed and fold it.
         // Returns false once the tail has ended (wave-uniform).
-        auto tail_row = [&](int t, int r, R cpr, R cpr1, R tp, R tq, R hq, R hp) -> bool {
+        auto tail_row = [&](int t, int r, R cpr, R cpr1, R tp, R tq, R hq, R hp) SK_INLINE -> bool {
             const R arp = fma(cpr, hq, tp), arq = fma(cpr, hp, tq);
             if (!FIXT) {
                 const R tail = (R)2 * tab.rmax[t] * (sk_abs(arp) + sk_abs(arq));
@@ -503,9 +598,10 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
 // The rows up to N take their Hankel part as w_r eb_r against r!/(r+k)!
 // (c^r/(r+k)! = w_r r!/(r+k)!), so they need only w_m = c^m/m!, which the
 // forward replay of the same cell can hand over (Wpre, nullable: m = 1..N);
-// tail rows continue c^m from w_N N!.
-template <typename R, int N, int TMAX, int DS = 1>
-__device__ __forceinline__ void sk_cell_adj(R c, int T, const SkTab<R>& tab, const R (&a)[N + 1],
+// tail rows continue c^m from w_N N!.  SMALL: the transpose of the small-|c|
+// rows, without tail rows (Wpre: m = 1..3).
+template <typename R, int N, int TMAX, int DS = 1, int SMALL = SK_SMALL_OFF>
+__device__ __forceinline__ void sk_cell_adj(R c, int T, SkTabArg<R>& tab, const R (&a)[N + 1],
                                             const R (&b)[N + 1], const R* DP, const R* DQ,
                                             R (&aP)[N + 1], R (&aQ)[N + 1], R& g,
                                             const R* Wpre = nullptr) {
@@ -513,13 +609,14 @@ __device__ __forceinline__ void sk_cell_adj(R c, int T, const SkTab<R>& tab, con
     R w[M + 1], cp[M + 1];
     w[0] = (R)1;
     cp[0] = (R)1;
-    auto power = [&](int m) {
+    auto power = [&](int m) SK_INLINE {
         if (m == N + 1) cp[N] = w[N] * (R)(1.0 / sk_inv_fact(N));
         cp[m] = cp[m - 1] * c;
         w[m] = cp[m] * ifact<R>(m);  // gradients need FP32 accuracy only
     };
+    constexpr int M0 = SMALL != SK_SMALL_OFF ? SK_SMALL_M : N;
 #pragma unroll
-    for (int m = 1; m <= N; ++m)  // tail rows compute theirs as they go
+    for (int m = 1; m <= M0; ++m)  // tail rows compute theirs as they go
         w[m] = Wpre ? Wpre[m - 1] : (m == 1 ? c : w[m - 1] * (c * (R)(1.0 / m)));
     // row 0 initialises the outputs (w_0 = c^0 = 1)
     aP[0] = a[0];
@@ -533,37 +630,61 @@ __device__ __forceinline__ void sk_cell_adj(R c, int T, const SkTab<R>& tab, con
     // T is the same in every lane; reading it into a scalar register makes
     // the early exit a branch instead of masked execution of every tail row
     const int Tu = __builtin_amdgcn_readfirstlane(T);
+    // row r, 1 <= r <= N, from the weights w_1 .. w_MT
+    auto row = [&](int r, int MT) SK_INLINE {
+        const R ea = a[r], eb = b[r];
+        gacc = r == 1 ? ea * DP[0] : fma(ea, DP[(r - 1) * DS], gacc);
+        gacc = fma(eb, DQ[(r - 1) * DS], gacc);
 #pragma unroll
-    for (int r = 1; r <= M; ++r) {
-        if (r > N && r - N > Tu) break;
-        if (r > N) power(r);
-        R ea, eb;
-        if (r <= N) {
-            ea = a[r];
-            eb = b[r];
-        } else {
-            ea = tab.rs[0][r - N - 1] * a[0];
-            eb = tab.rs[0][r - N - 1] * b[0];
+        for (int k = r; k >= 0; --k) {
+            if (r - k > MT) break;
+            aP[k] = fma(w[r - k], ea, aP[k]);
+            aQ[k] = fma(w[r - k], eb, aQ[k]);
+        }
+        if (r > MT) return;  // (small |c|: no Hankel part)
+        const R cb = w[r] * eb, ca = w[r] * ea;
+#pragma unroll
+        for (int k = 1; k <= N; ++k) {
+            const R f = (R)(sk_inv_fact(r + k) / sk_inv_fact(r));
+            aP[k] = fma(cb, f, aP[k]);
+            aQ[k] = fma(ca, f, aQ[k]);
+        }
+    };
+    const bool full = SMALL == SK_SMALL_OFF ||
+                      (SMALL == SK_SMALL_ASK &&
+                       (__builtin_amdgcn_ballot_w64(!(sk_abs(c) <= (R)SK_SMALL_C)) != 0 || Tu > 0));
+    if (!full) {
+#pragma unroll
+        for (int r = 1; r <= N; ++r) row(r, SK_SMALL_M);
+    } else {
+#pragma unroll
+        for (int m = M0 + 1; m <= N; ++m) w[m] = w[m - 1] * (c * (R)(1.0 / m));
+#pragma unroll
+        for (int r = 1; r <= N; ++r) row(r, N);
+#pragma unroll
+        for (int r = N + 1; r <= M; ++r) {  // tail rows
+            if (r - N > Tu) break;
+            power(r);
+            R ea = tab.rs[0][r - N - 1] * a[0];
+            R eb = tab.rs[0][r - N - 1] * b[0];
 #pragma unroll
             for (int n = 1; n <= N; ++n) {
                 ea = fma(tab.rs[n][r - N - 1], a[n], ea);
                 eb = fma(tab.rs[n][r - N - 1], b[n], eb);
             }
-        }
-        gacc = r == 1 ? ea * DP[0] : fma(ea, DP[(r - 1) * DS], gacc);
-        gacc = fma(eb, DQ[(r - 1) * DS], gacc);
+            gacc = fma(ea, DP[(r - 1) * DS], gacc);
+            gacc = fma(eb, DQ[(r - 1) * DS], gacc);
 #pragma unroll
-        for (int k = (r < N ? r : N); k >= 0; --k) {
-            aP[k] = fma(w[r - k], ea, aP[k]);
-            aQ[k] = fma(w[r - k], eb, aQ[k]);
-        }
-        const R hw = r <= N ? w[r] : cp[r];
-        const R cb = hw * eb, ca = hw * ea;
+            for (int k = N; k >= 0; --k) {
+                aP[k] = fma(w[r - k], ea, aP[k]);
+                aQ[k] = fma(w[r - k], eb, aQ[k]);
+            }
+            const R cb = cp[r] * eb, ca = cp[r] * ea;
 #pragma unroll
-        for (int k = 1; k <= N; ++k) {
-            const R f = r <= N ? (R)(sk_inv_fact(r + k) / sk_inv_fact(r)) : ifact<R>(r + k);
-            aP[k] = fma(cb, f, aP[k]);
-            aQ[k] = fma(ca, f, aQ[k]);
+            for (int k = 1; k <= N; ++k) {
+                aP[k] = fma(cb, ifact<R>(r + k), aP[k]);
+                aQ[k] = fma(ca, ifact<R>(r + k), aQ[k]);
+            }
         }
     }
     g = gacc;
@@ -576,7 +697,7 @@ __device__ __forceinline__ void sk_cell_adj(R c, int T, const SkTab<R>& tab, con
 // adjoints keep derivatives for (SkTailReg); T > TMAX (a cell past the
 // compiled cap in the forward) gives g = NaN.
 template <typename R, int N, int TMAX>
-__device__ __forceinline__ void sk_cell_adj_in(R c, int T, const SkTab<R>& tab, const R (&a)[N + 1],
+__device__ __forceinline__ void sk_cell_adj_in(R c, int T, SkTabArg<R>& tab, const R (&a)[N + 1],
                                                const R (&b)[N + 1], const R (&P)[N + 1],
                                                const R (&Q)[N + 1], R (&aP)[N + 1],
                                                R (&aQ)[N + 1], R& g) {

@@ -4,6 +4,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "sk_common.h"
 #include "sk_device.h"
 
@@ -14,6 +16,14 @@ typedef short sk_s4 __attribute__((ext_vector_type(4)));  // 4 bf16 bit patterns
 // ---------------------------------------------------------------------------
 // small utilities
 // ---------------------------------------------------------------------------
+// The kernel's argument struct (its only argument) where the hardware put it:
+// its tables, indexed at run time, are read from there, not from a copy in
+// scratch.
+template <typename A>
+__device__ __forceinline__ const SK_KARG A& sk_kernarg() {
+    return *(const SK_KARG A*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 template <typename T>
 __global__ void k_fill(T* p, int64_t n, T v) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -642,6 +652,17 @@ struct SweepArgs {
     int32_t S;             // checkpoint stride of the checkpointing sweep
 };
 
+// A value, or the lane index, as one the compiler knows nothing about: what is
+// derived from it (a block end's divisions by record sizes, the seed's
+// coefficients) is computed where it is used and not kept in registers through
+// the steps, or spilled and reloaded behind every store in flight.
+template <typename T>
+__device__ __forceinline__ T sk_value_here(T v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ int sk_lane_here(int r) { return sk_value_here(r); }
+
 // Global strip-boundary exchange, consumer side: at the start of every
 // 8-step block the wave (1) fences, so that the records stored by the
 // producing lane in earlier blocks are visible, (2) moves the records it
@@ -655,7 +676,8 @@ struct SweepArgs {
 // read with device-coherent loads.
 template <int W, bool COHERENT = false, typename F>
 __device__ __forceinline__ void sk_gx_stage(unsigned (&xr)[(8 * W + 63) / 64], unsigned* stage,
-                                            const unsigned* xg, int t_next, int r, F want) {
+                                            const unsigned* xg, int t_next, int lane, F want) {
+    const int r = sk_lane_here(lane);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
 #pragma unroll
     for (int h = 0; h < (8 * W + 63) / 64; ++h)
@@ -749,7 +771,11 @@ __device__ __forceinline__ void sk_edge_write(SkLds<unsigned> rec, double q0, do
 // global exchange (compiled separately so launches without such pairs keep
 // their register budget).
 template <typename R, int N, int TMAX, bool CKPT, int S, bool GX>
-__global__ __launch_bounds__(64) void k_sweep(const SweepArgs<R> a) {
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(
+    sizeof(R) == 8 ? (TMAX == 0 && N <= 6 ? 3 : 1) : (TMAX == 0 || N <= 6) && !(CKPT && GX && N >= 6) ? 4 : 3, 8)))
+void k_sweep(const SweepArgs<R> a) {
+    SkTabArg<R>& tab = sk_kernarg<SweepArgs<R>>().tab;
     const int r = threadIdx.x;
     const int64_t local = blockIdx.x;
     const SkPairDesc pd = sk_pair(a.src, local);
@@ -772,14 +798,15 @@ __global__ __launch_bounds__(64) void k_sweep(const SweepArgs<R> a) {
     // current 8-step block in LDS ([8][GXW], before the ring), for the
     // adjoint's copy of the boundary edges
     constexpr int OST = (GX && CKPT) ? sk_gx_stage_bytes(N, ES) : 0;
-    const SkLds<unsigned> ost = (SkLds<unsigned>)(sk_smem + sk_gx_stage_bytes(N, ES));
-    const SkLds<unsigned> ring = (SkLds<unsigned>)(sk_smem + sk_gx_stage_bytes(N, ES) + OST);  // [ly][RW]
+    constexpr int STG = GX ? sk_gx_stage_bytes(N, ES) : 0;  // (no staging slot without the exchange)
+    const SkLds<unsigned> ost = (SkLds<unsigned>)(sk_smem + STG);
+    const SkLds<unsigned> ring = (SkLds<unsigned>)(sk_smem + STG + OST);  // [ly][RW]
     unsigned* xg = a.xb + pd.xb_off;  // [ly][GXW] (exchange pairs only)
     unsigned xr[(8 * GXW + 63) / 64];
 #pragma unroll
     for (int h = 0; h < (8 * GXW + 63) / 64; ++h) xr[h] = 0u;
     // column lane 0 reads at step tau (strips >= 1), or -1
-    auto lane0_col = [&](int tau) -> int {
+    auto lane0_col = [&](int tau) SK_INLINE -> int {
         const int s0 = tau / g.Tp, j0 = tau - s0 * g.Tp;
         return (tau < g.nsteps && s0 >= 1 && s0 < g.nstrips && j0 < g.ly) ? j0 : -1;
     };
@@ -810,143 +837,185 @@ __global__ __launch_bounds__(64) void k_sweep(const SweepArgs<R> a) {
     R cb[8], cn[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) cb[u] = cs[u * 64 + r];
+    // steps unrolled together: few where a pair would run through cold
+    // instructions for as long as it computes (interpolation; general blocks,
+    // of which most pairs have one: 408 pairs of 49 x 40 cells, FP32 order 4,
+    // sweep 106 us with 8 steps of both kinds, 96 with 4)
+    constexpr int HF = TMAX == 0 ? 8 : 4, HG = 4;
     unsigned tword = 0u;  // tail lengths of the current checkpoint segment
-    for (int t0 = 0; t0 < nst8; t0 += 8) {
-        if (gx) sk_gx_stage<GXW>(xr, stage, xg, t0 + 8, r, lane0_col);
-        if (t0 + 8 < g.nsteps_pad) {
+    // FAST blocks: pairs whose strips follow each other without idle columns
+    // (Tp = ly, and more than 64 columns, so that the entry lane 0 reads one
+    // step ahead has been written), or of one strip.  There lane r is in column
+    // tT - r of strip sS, or, while r > tT, in column Tp + tT - r of strip
+    // sS - 1, (sS, tT) lane 0's place at the step, and the lanes' places, their tests and the selects of a
+    // lane that starts a row come down to one comparison in the blocks in
+    // which lanes enter a strip.  Lanes without a cell (before their first,
+    // after their last, past the pair's last row) have c = 0 and compute
+    // values that no cell reads.  Lane 0's edge of the next step is read from
+    // LDS one step ahead, and cells of small |c| take their shorter rows
+    // (SK_SMALL_C; where strips of several are all filled, as in the strip
+    // pipeline, whose values are the same to the last bit while no |c| is small).
+    const bool one_strip = g.nstrips == 1;  // no boundary edges: lane 0 starts from the initial edge
+    const bool fastp = one_strip || (g.Tp == g.ly && g.ly > 64);
+    const int Tf = one_strip ? 0x7fffffff : g.Tp;
+    R small_c = (R)SK_SMALL_C;
+    int tT = 0, jS = -63;  // FAST: the columns of lanes 0 and 63
+    const unsigned handed = (unsigned)((g.nstrips - 1) * g.Tp);  // cells whose right edge is handed on
+    int t0 = 0;
+    auto load_c = [&](int row) SK_INLINE {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) cn[u] = cs[(int64_t)(t0 + 8 + u) * 64 + r];
+        for (int u = 0; u < 8; ++u) cn[u] = cs[(int64_t)(row + u) * 64 + r];
+    };
+    // the next block's first row (the last block's constants are not used)
+    auto next_row = [&]() SK_INLINE { return t0 + 8 < g.nsteps_pad ? t0 + 8 : t0; };
+    // the pair's value, from the last cell's outputs (this lane's state)
+    auto write_value = [&]() SK_INLINE {
+        R kr = (R)0;
+#pragma unroll
+        for (int n = N; n >= 2; --n) kr = fma(P[n] + Qs[n], ifact<R>(n), kr);
+        const double kv = 0.5 * (P0 + Qs0 + P1 + Qs1 + (double)kr);
+        sk_write_k(a.K, a.Kexp, pd.k_idx, kv, E);
+    };
+    double B0 = 0.0, B1 = 0.0;  // lane 0's left edge of the step
+    R Bq[N + 1];
+    int Be = 0;
+    auto read_edge = [&](int u, int col, bool initial) SK_INLINE {
+        if (initial) {
+            B0 = 1.0;
+            B1 = 0.0;
+#pragma unroll
+            for (int n = 2; n <= N; ++n) Bq[n] = (R)0;
+            Be = 0;
+        } else {
+            sk_edge_read<R, N>(gx ? (SkLds<unsigned>)stage + u * GXW : ring + __mul24(col, RW), B0, B1, Bq, Be);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int tau = t0 + u;
-            // lane 0's left edge: the strip-boundary entry of its column (the
-            // ring, or the staged exchange record of this step), read alike by
-            // every lane and merged into the lane move that feeds lanes 1..63
+    };
+    // Step u of the block (um: among the steps unrolled together).
+    auto step = [&](int u, int um, R cu, auto fastc) SK_INLINE {
+        constexpr bool FAST = decltype(fastc)::value;
+        constexpr int SMALL = FAST && sk_small_path<R, N>() ? SK_SMALL_ASK : SK_SMALL_OFF;
+        const int tau = t0 + u, tN = tT + 1 == Tf ? 0 : tT + 1;
+        // lane 0's left edge: the strip-boundary entry of its column (the
+        // ring, or the staged exchange record of this step), read alike by
+        // every lane and merged into the lane move that feeds lanes 1..63
+        if (FAST) {
+            if (GX && um == 0 && u == 0) read_edge(0, tT, one_strip || (gx && tau < g.Tp));
+        } else {
             const int j0 = __builtin_amdgcn_readfirstlane(j), s0 = __builtin_amdgcn_readfirstlane(s);
-            double B0, B1;
-            R Bq[N + 1];
-            int Be;
-            sk_edge_read<R, N>(gx ? (SkLds<unsigned>)stage + u * GXW
-                                  : ring + __mul24(j0 < g.ly ? j0 : g.ly - 1, RW),
-                               B0, B1, Bq, Be);
-            if (gx && s0 == 0) {
-                B0 = 1.0;
-                B1 = 0.0;
+            read_edge(u, j0 < g.ly ? j0 : g.ly - 1, one_strip || (gx && s0 == 0));
+        }
+        R Qin[N + 1];
 #pragma unroll
-                for (int n = 2; n <= N; ++n) Bq[n] = (R)0;
-                Be = 0;
-            }
-            R Qin[N + 1];
+        for (int n = 2; n <= N; ++n) Qin[n] = lane_from_prev_or(Qs[n], Bq[n]);
+        double Qin0 = lane_from_prev_or(Qs0, B0), Qin1 = lane_from_prev_or(Qs1, B1);
+        int Ein = lane_from_prev_or(Es, Be);
+        if (FAST && (!GX || um < HF - 1 || u < 7))  // (one step ahead; staged records are a block's)
+            read_edge(u + 1, tN, one_strip || (gx && tau + 1 < g.Tp));
+        const int i = s * 64 + r;
+        if (!FAST) live = (L >= 0) && (s < g.nstrips) && (j < g.ly) && (i < g.lx);
+        auto start_row = [&]() SK_INLINE {
+            P0 = 1.0;
+            P1 = 0.0;
 #pragma unroll
-            for (int n = 2; n <= N; ++n) Qin[n] = lane_from_prev_or(Qs[n], Bq[n]);
-            double Qin0 = lane_from_prev_or(Qs0, B0), Qin1 = lane_from_prev_or(Qs1, B1);
-            int Ein = lane_from_prev_or(Es, Be);
-            const int i = s * 64 + r;
-            live = (L >= 0) && (s < g.nstrips) && (j < g.ly) && (i < g.lx);
-            if (live) {
-                if (j == 0) {
-                    P0 = 1.0;
-                    P1 = 0.0;
-#pragma unroll
-                    for (int n = 2; n <= N; ++n) P[n] = (R)0;
-                    E = 0;
-                }
+            for (int n = 2; n <= N; ++n) P[n] = (R)0;
+            E = 0;
+        };
+        if (FAST && tT < 64) {  // (a branch: the lane's copy keeps it from becoming nine masked moves a step)
+            if (sk_lane_here(r) == tT) start_row();
+        }
+        if (FAST || live) {
+            if (!FAST && j == 0) start_row();
+            if (sk_wave_any(E != Ein)) {  // rare: skip in the common case
                 const int Ec = E > Ein ? E : Ein;
                 const int dp = E - Ec, dq = Ein - Ec;
-                if (sk_wave_any(dp != 0 || dq != 0)) {  // rare: skip in the common case
-                    P0 = ldexp(P0, dp);
-                    P1 = ldexp(P1, dp);
-                    Qin0 = ldexp(Qin0, dq);
-                    Qin1 = ldexp(Qin1, dq);
+                P0 = ldexp(P0, dp);
+                P1 = ldexp(P1, dp);
+                Qin0 = ldexp(Qin0, dq);
+                Qin1 = ldexp(Qin1, dq);
 #pragma unroll
-                    for (int n = 2; n <= N; ++n) {
-                        P[n] = sk_ldexp(P[n], dp);
-                        Qin[n] = sk_ldexp(Qin[n], dq);
-                    }
+                for (int n = 2; n <= N; ++n) {
+                    P[n] = sk_ldexp(P[n], dp);
+                    Qin[n] = sk_ldexp(Qin[n], dq);
                 }
                 E = Ec;
             }
-            P[0] = (R)P0;
-            P[1] = (R)P1;
-            Qin[0] = (R)Qin0;
-            Qin[1] = (R)Qin1;
-            if (CKPT && (tau % S) == 0 && tau < g.nsteps) {
-                const int64_t kk = tau / S;
-                R* ck = a.ck + pd.ck_off + kk * 2 * (N + 1) * 64;
-#pragma unroll
-                for (int n = 0; n <= N; ++n) {
-                    sk_st_nt(ck + n * 64 + r, P[n]);
-                    sk_st_nt(ck + (N + 1 + n) * 64 + r, Qin[n]);
-                }
-                sk_st_nt(a.ce + pd.ce_off + kk * (SK_LANES + 1) + r, E);
-            }
-            R Po[N + 1], Qo[N + 1];
-            double Po0, Po1, Qo0, Qo1;
-            int Tc = 0;
-            sk_cell_fwd<R, N, TMAX>(P, Qin, P0, P1, Qin0, Qin1, cb[u], live, a.tab, Po, Qo, Po0,
-                                    Po1, Qo0, Qo1, nullptr, nullptr,
-                                    (CKPT && TMAX > 0) ? &Tc : nullptr);
-            if (CKPT && TMAX > 0) {
-                // the adjoint's replay folds the same tail rows
-                tword |= (unsigned)Tc << (8 * (u % S));
-                if (u % S == S - 1) {
-                    if (r == 0 && tau - (S - 1) < g.nsteps)
-                        a.ce[pd.ce_off + (int64_t)(tau / S) * (SK_LANES + 1) + SK_LANES] = (int)tword;
-                    tword = 0u;
-                }
-            }
+        }
+        P[0] = (R)P0;
+        P[1] = (R)P1;
+        Qin[0] = (R)Qin0;
+        Qin[1] = (R)Qin1;
+        if (CKPT && (um % S) == 0 && (FAST || tau < g.nsteps)) {
+            const int64_t kk = tau / S;
+            R* ck = a.ck + pd.ck_off + kk * 2 * (N + 1) * 64;
 #pragma unroll
             for (int n = 0; n <= N; ++n) {
-                P[n] = Po[n];
-                Qs[n] = Qo[n];
+                sk_st_nt(ck + n * 64 + r, P[n]);
+                sk_st_nt(ck + (N + 1 + n) * 64 + r, Qin[n]);
             }
-            P0 = Po0;
-            P1 = Po1;
-            Qs0 = Qo0;
-            Qs1 = Qo1;
-            Es = E;
-            if (live) {
-                if (r == 63 && s + 1 < g.nstrips) {
-                    if (gx) {
-                        // the record in 16-byte stores (records are 16-byte
-                        // aligned, GXW words each)
-                        constexpr int NW = 4 + (N - 1) * (ES / 4) + 1, NQ = (NW + 3) / 4;
-                        unsigned wd[4 * NQ];
-                        wd[0] = (unsigned)__double2loint(Qo0);
-                        wd[1] = (unsigned)__double2hiint(Qo0);
-                        wd[2] = (unsigned)__double2loint(Qo1);
-                        wd[3] = (unsigned)__double2hiint(Qo1);
+            sk_st_nt(a.ce + pd.ce_off + kk * (SK_LANES + 1) + r, E);
+        }
+        R Po[N + 1], Qo[N + 1];
+        double Po0, Po1, Qo0, Qo1;
+        int Tc = 0;
+        sk_cell_fwd<R, N, TMAX, false, true, false, 1, SMALL>(
+            P, Qin, P0, P1, Qin0, Qin1, cu, FAST || live, tab, Po, Qo, Po0, Po1, Qo0, Qo1,
+            nullptr, nullptr, (CKPT && TMAX > 0) ? &Tc : nullptr, 0, nullptr, small_c);
+        if (CKPT && TMAX > 0) {
+            // the adjoint's replay folds the same tail rows
+            tword |= (unsigned)Tc << (8 * (um % S));
+            if (um % S == S - 1) {
+                if (r == 0 && (FAST || tau - (S - 1) < g.nsteps))
+                    a.ce[pd.ce_off + (int64_t)(tau / S) * (SK_LANES + 1) + SK_LANES] = (int)tword;
+                tword = 0u;
+            }
+        }
 #pragma unroll
-                        for (int n = 2; n <= N; ++n) {
-                            if constexpr (ES == 4) {
-                                wd[4 + n - 2] = __float_as_uint(Qo[n]);
-                            } else {
-                                wd[4 + 2 * (n - 2)] = (unsigned)__double2loint(Qo[n]);
-                                wd[4 + 2 * (n - 2) + 1] = (unsigned)__double2hiint(Qo[n]);
-                            }
-                        }
-                        wd[NW - 1] = (unsigned)E;
+        for (int n = 0; n <= N; ++n) {
+            P[n] = Po[n];
+            Qs[n] = Qo[n];
+        }
+        P0 = Po0;
+        P1 = Po1;
+        Qs0 = Qo0;
+        Qs1 = Qo1;
+        Es = E;
+        const int jc = FAST ? jS : j;  // lane 63's column
+        if (r == 63 && (FAST ? (unsigned)(tau - 63) < handed : live && s + 1 < g.nstrips)) {
+            if (gx) {
+                // the record in 16-byte stores (records are 16-byte
+                // aligned, GXW words each)
+                constexpr int NW = 4 + (N - 1) * (ES / 4) + 1, NQ = (NW + 3) / 4;
+                unsigned wd[4 * NQ];
+                wd[0] = (unsigned)__double2loint(Qo0);
+                wd[1] = (unsigned)__double2hiint(Qo0);
+                wd[2] = (unsigned)__double2loint(Qo1);
+                wd[3] = (unsigned)__double2hiint(Qo1);
 #pragma unroll
-                        for (int k = NW; k < 4 * NQ; ++k) wd[k] = 0u;
-                        uint4* rec = reinterpret_cast<uint4*>(xg + (int64_t)j * GXW);
-#pragma unroll
-                        for (int k = 0; k < NQ; ++k)
-                            rec[k] = make_uint4(wd[4 * k], wd[4 * k + 1], wd[4 * k + 2], wd[4 * k + 3]);
-                        // (the checkpoint copy leaves once per block, from LDS)
-                        if (CKPT) sk_edge_write<R, N>(ost + u * GXW, Qo0, Qo1, Qo, E);
+                for (int n = 2; n <= N; ++n) {
+                    if constexpr (ES == 4) {
+                        wd[4 + n - 2] = __float_as_uint(Qo[n]);
                     } else {
-                        // (the checkpoint copy of ring entries leaves once per block)
-                        sk_edge_write<R, N>(ring + __mul24(j, RW), Qo0, Qo1, Qo, E);
+                        wd[4 + 2 * (n - 2)] = (unsigned)__double2loint(Qo[n]);
+                        wd[4 + 2 * (n - 2) + 1] = (unsigned)__double2hiint(Qo[n]);
                     }
                 }
-                if (i == g.lx - 1 && j == g.ly - 1) {
-                    R kr = (R)0;
+                wd[NW - 1] = (unsigned)E;
 #pragma unroll
-                    for (int n = N; n >= 2; --n) kr = fma(Po[n] + Qo[n], ifact<R>(n), kr);
-                    const double kv = 0.5 * (Po0 + Qo0 + Po1 + Qo1 + (double)kr);
-                    sk_write_k(a.K, a.Kexp, pd.k_idx, kv, E);
-                }
+                for (int k = NW; k < 4 * NQ; ++k) wd[k] = 0u;
+                uint4* rec = reinterpret_cast<uint4*>(xg + (int64_t)jc * GXW);
+#pragma unroll
+                for (int k = 0; k < NQ; ++k)
+                    rec[k] = make_uint4(wd[4 * k], wd[4 * k + 1], wd[4 * k + 2], wd[4 * k + 3]);
+                // (the checkpoint copy leaves once per block, from LDS)
+                if (CKPT) sk_edge_write<R, N>(ost + u * GXW, Qo0, Qo1, Qo, E);
+            } else {
+                // (the checkpoint copy of ring entries leaves once per block)
+                sk_edge_write<R, N>(ring + __mul24(jc, RW), Qo0, Qo1, Qo, E);
+            }
+        }
+        if (!FAST) {
+            if (live && i == g.lx - 1 && j == g.ly - 1) {
+                write_value();
             }
             if (L >= 0) {
                 if (++j == g.Tp) {
@@ -955,7 +1024,29 @@ __global__ __launch_bounds__(64) void k_sweep(const SweepArgs<R> a) {
                 }
             }
             ++L;
+        } else {
+            tT = tN;
+            jS = jS + 1 == Tf ? 0 : jS + 1;
         }
+    };
+    // the steps of a block, HU at a time
+    auto steps = [&](auto fastc) SK_INLINE {
+        constexpr int HU = decltype(fastc)::value ? HF : HG;
+#pragma unroll 1
+        for (int h = 0; h < 8; h += HU) {
+            R cg[HU];
+#pragma unroll
+            for (int u = 0; u < HU; ++u) cg[u] = HU == 8 || h == 0 ? cb[u] : cb[8 - HU + u];
+#pragma unroll
+            for (int u = 0; u < HU; ++u) step(h + u, u, cg[u], fastc);
+        }
+    };
+    auto block_end = [&](auto fastc) SK_INLINE {
+        constexpr bool FAST = decltype(fastc)::value;
+        // (before the boundary edges' stores: the wait for the constants does
+        // not include them)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) cb[u] = cn[u];
         // the strip-boundary edges lane 63 handed over in this block, from
         // the ring (an entry is rewritten only Tp >= 64 steps after it was
         // written) or, for exchange pairs, the block's LDS staging, to the
@@ -963,21 +1054,31 @@ __global__ __launch_bounds__(64) void k_sweep(const SweepArgs<R> a) {
         if (CKPT) {
             // lane 63's place after the block: the place of step t0 + u is
             // 8 - u columns back (while L >= 0 it advanced every step)
-            const int Le = __builtin_amdgcn_readlane(L, 63), se = __builtin_amdgcn_readlane(s, 63),
-                      je = __builtin_amdgcn_readlane(j, 63);
+            int Le, se, je;
+            if (FAST) {
+                Le = t0 + 8 - 63;
+                je = jS;
+                se = 0;  // (not used)
+            } else {
+                Le = __builtin_amdgcn_readlane(L, 63);
+                se = __builtin_amdgcn_readlane(s, 63);
+                je = __builtin_amdgcn_readlane(j, 63);
+            }
             constexpr int QR = N + 2;  // N + 1 coefficients and the exponent
+            const int rh = sk_lane_here(r);
 #pragma unroll
             for (int e0 = 0; e0 < 8 * QR; e0 += 64) {
-                const int e = e0 + r, u = e / QR, w = e - u * QR;
+                const int e = e0 + rh, u = e / QR, w = e - u * QR;
                 const int back = 8 - u;
                 int jc = je - back, sc = se;
                 if (jc < 0) {
                     jc += g.Tp;
                     --sc;
                 }
-                if (e < 8 * QR && Le - back >= 0 && sc + 1 < g.nstrips && jc < g.ly) {
+                if (e < 8 * QR && (FAST ? (unsigned)(Le - back) < handed
+                                        : Le - back >= 0 && sc + 1 < g.nstrips && jc < g.ly)) {
                     const SkLds<unsigned> rec = gx ? ost + u * GXW : ring + __mul24(jc, RW);
-                    const int64_t o = (int64_t)(sc + 1) * g.ly + jc;
+                    const int64_t o = FAST ? (int64_t)(Le - back) + g.ly : (int64_t)(sc + 1) * g.ly + jc;
                     if (w <= N) {
                         R v;
                         if (w < 2)
@@ -992,7 +1093,7 @@ __global__ __launch_bounds__(64) void k_sweep(const SweepArgs<R> a) {
             }
         }
         // per-lane rescale of the live state
-        if (live) {
+        if (FAST || live) {
             R m = (R)fmax(fmax(fabs(P0), fabs(Qs0)), fmax(fabs(P1), fabs(Qs1)));
 #pragma unroll
             for (int n = 2; n <= N; ++n) {
@@ -1015,8 +1116,33 @@ __global__ __launch_bounds__(64) void k_sweep(const SweepArgs<R> a) {
                 Es = E;
             }
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) cb[u] = cn[u];
+        t0 += 8;
+    };
+    // The fast blocks run in a loop of their own: the vector memory operations
+    // of its body are then counted exactly, so that waiting for the constants
+    // loaded one block ahead does not wait for younger loads and checkpoint
+    // stores (behind a branch the count is unknown and every block drained
+    // them all).
+    if (fastp) {
+        read_edge(0, 0, GX || one_strip);
+        __builtin_amdgcn_s_waitcnt(sk_waitcnt_vm0());
+        while (t0 + 8 <= g.nsteps) {
+            if (gx) sk_gx_stage<GXW>(xr, stage, xg, t0 + 8, r, lane0_col);
+            load_c(next_row());
+            small_c = one_strip || (t0 >= 64 && t0 + 8 <= g.nstrips * g.Tp) ? (R)SK_SMALL_C : (R)-1;
+            steps(std::true_type{});
+            if (t0 + 8 == g.nsteps && r == ((g.lx - 1) & 63)) write_value();
+            block_end(std::true_type{});
+        }
+        L = t0 - r;
+        s = L >= 0 ? L / g.Tp : 0;
+        j = L >= 0 ? L - s * g.Tp : 0;
+    }
+    while (t0 < nst8) {
+        if (gx) sk_gx_stage<GXW>(xr, stage, xg, t0 + 8, r, lane0_col);
+        load_c(next_row());
+        steps(std::false_type{});
+        block_end(std::false_type{});
     }
 }
 
@@ -1090,9 +1216,15 @@ __device__ __forceinline__ void sk_stores_complete() {
 }
 
 // Wave-uniform bounded wait until *prog >= need.  Returns false on abort.
-__device__ __forceinline__ bool sk_wait_count(const int* prog, int need, int* abort, int limit) {
+// `seen` is the last count read (counts only grow): a count that already
+// covers the need is not read again, which spares a strip whose producer has
+// run ahead a load and its drain of the wave's memory operations every block.
+__device__ __forceinline__ bool sk_wait_count(const int* prog, int need, int& seen, int* abort, int limit) {
+    if (seen >= need) return true;
     for (int it = 0;; ++it) {
-        if (__hip_atomic_load(prog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need) {
+        seen = __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(prog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (seen >= need) {
             __atomic_signal_fence(__ATOMIC_SEQ_CST);  // record loads stay after the poll
             return true;
         }
@@ -1108,7 +1240,10 @@ __device__ __forceinline__ bool sk_wait_count(const int* prog, int need, int* ab
 }
 
 template <typename R, int N, int TMAX, bool CKPT, int S>
-__global__ __launch_bounds__(64) void k_sweep_pipe(const PipeArgs<R> a) {
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 1 : CKPT && N >= 5 ? 3 : TMAX == 0 || N <= 6 ? 4 : 3, 8)))
+void k_sweep_pipe(const PipeArgs<R> a) {
+    SkTabArg<R>& tab = sk_kernarg<PipeArgs<R>>().tab;
     const int r = threadIdx.x;
     constexpr int ES = (int)sizeof(R), GXW = sk_gx_words(N, ES);
     constexpr int XR = (8 * GXW + 63) / 64;
@@ -1118,6 +1253,7 @@ __global__ __launch_bounds__(64) void k_sweep_pipe(const PipeArgs<R> a) {
     // slot by all lanes at the block's end (before it is published)
     const SkLds<unsigned> ost = (SkLds<unsigned>)(sk_smem + sk_gx_stage_bytes(N, ES));  // [8][GXW]
     constexpr int NW = 4 + (N - 1) * (ES / 4) + 1;  // words of a record
+    constexpr int HU = TMAX == 0 ? 8 : 4;  // steps unrolled together (as in k_sweep)
     for (int64_t q = blockIdx.x; q < a.njobs; q += gridDim.x) {
         // the job: strip s of a pair with geometry g and arrays at these bases
         const int2 jb = a.jobs[q];
@@ -1131,7 +1267,7 @@ __global__ __launch_bounds__(64) void k_sweep_pipe(const PipeArgs<R> a) {
         const int ly = g.ly;
         const int nloc = sk_pipe_steps(ly);
         // lane 0 reads column t at local step t
-        auto col0 = [&](int t) -> int { return t < ly ? t : -1; };
+        auto col0 = [&](int t) SK_INLINE -> int { return t < ly ? t : -1; };
         const int i = s * 64 + r;
         const bool rowok = i < g.lx;
         const bool has_next = s + 1 < g.nstrips;
@@ -1159,8 +1295,9 @@ __global__ __launch_bounds__(64) void k_sweep_pipe(const PipeArgs<R> a) {
 #pragma unroll
         for (int h = 0; h < XR; ++h) xr[h] = 0u;
         bool ok = true;
+        int seen = 0;  // last count read of strip s-1
         if (s > 0) {  // records of columns 0..7
-            ok = sk_wait_count(prog + s - 1, ly < 8 ? ly : 8, a.abort, a.spin_limit);
+            ok = sk_wait_count(prog + s - 1, ly < 8 ? ly : 8, seen, a.abort, a.spin_limit);
             if (ok) {
 #pragma unroll
                 for (int h = 0; h < XR; ++h) {
@@ -1176,137 +1313,155 @@ __global__ __launch_bounds__(64) void k_sweep_pipe(const PipeArgs<R> a) {
             }
         }
         int published = 0;
-        for (int t0 = 0; ok && t0 < nloc; t0 += 8) {
-            if (s > 0) {
-                const int need = t0 + 16 < ly ? t0 + 16 : ly;
-                ok = sk_wait_count(prog + s - 1, need, a.abort, a.spin_limit);
-                if (!ok) break;
-                sk_gx_stage<GXW, true>(xr, stage, rin, t0 + 8, r, col0);
-            }
-            R cb[8];
+        bool live = false;
+        int t0 = 0;
+        // cell constants, loaded one block ahead (rows past the pair's last
+        // are not used: their steps have no live lane)
+        R cb[8], cn[8];
+        auto load_c = [&](R (&v)[8], int row) SK_INLINE {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) cb[u] = (t0 + u < rows_left) ? cs[(int64_t)(t0 + u) * 64 + r] : (R)0;
-            bool live = false;
+            for (int u = 0; u < 8; ++u)
+                v[u] = cs[(row + u < rows_left ? (int64_t)(row + u) : rows_left - 1) * 64 + r];
+        };
+        load_c(cb, 0);
+        // Step u of the block (um = u modulo HU).  FAST: a block in which every lane is inside the
+        // strip, past its first column and before its last (see k_sweep).
+        auto step = [&](int u, int um, R cu, auto fastc) SK_INLINE {
+            constexpr bool FAST = decltype(fastc)::value;
+            constexpr int SMALL = FAST && sk_small_path<R, N>() ? SK_SMALL_ASK : SK_SMALL_OFF;
+            const int t = t0 + u, j = t - r;
+            R Qin[N + 1];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int t = t0 + u, j = t - r;
-                R Qin[N + 1];
+            for (int n = 2; n <= N; ++n) Qin[n] = lane_from_prev(Qs[n]);
+            double Qin0 = lane_from_prev(Qs0), Qin1 = lane_from_prev(Qs1);
+            int Ein = lane_from_prev(Es);
+            live = FAST || (rowok && j >= 0 && j < ly);
+            if (live) {
+                if (!FAST && j == 0) {
+                    P0 = 1.0;
+                    P1 = 0.0;
 #pragma unroll
-                for (int n = 2; n <= N; ++n) Qin[n] = lane_from_prev(Qs[n]);
-                double Qin0 = lane_from_prev(Qs0), Qin1 = lane_from_prev(Qs1);
-                int Ein = lane_from_prev(Es);
-                live = rowok && j >= 0 && j < ly;
-                if (live) {
-                    if (j == 0) {
-                        P0 = 1.0;
-                        P1 = 0.0;
+                    for (int n = 2; n <= N; ++n) P[n] = (R)0;
+                    E = 0;
+                }
+                if (r == 0) {
+                    if (s == 0) {
+                        Qin0 = 1.0;
+                        Qin1 = 0.0;
 #pragma unroll
-                        for (int n = 2; n <= N; ++n) P[n] = (R)0;
-                        E = 0;
+                        for (int n = 2; n <= N; ++n) Qin[n] = (R)0;
+                        Ein = 0;
+                    } else {
+                        sk_edge_read<R, N>((SkLds<unsigned>)stage + u * GXW, Qin0, Qin1, Qin, Ein);
                     }
-                    if (r == 0) {
-                        if (s == 0) {
-                            Qin0 = 1.0;
-                            Qin1 = 0.0;
-#pragma unroll
-                            for (int n = 2; n <= N; ++n) Qin[n] = (R)0;
-                            Ein = 0;
-                        } else {
-                            const unsigned* rec = stage + u * GXW;
-                            Qin0 = *reinterpret_cast<const double*>(rec);
-                            Qin1 = *reinterpret_cast<const double*>(rec + 2);
-#pragma unroll
-                            for (int n = 2; n <= N; ++n)
-                                Qin[n] = *reinterpret_cast<const R*>(rec + 4 + (n - 2) * (ES / 4));
-                            Ein = (int)rec[4 + (N - 1) * (ES / 4)];
-                        }
-                    }
+                }
+                if (sk_wave_any(E != Ein)) {
                     const int Ec = E > Ein ? E : Ein;
                     const int dp = E - Ec, dq = Ein - Ec;
-                    if (sk_wave_any(dp != 0 || dq != 0)) {
-                        P0 = ldexp(P0, dp);
-                        P1 = ldexp(P1, dp);
-                        Qin0 = ldexp(Qin0, dq);
-                        Qin1 = ldexp(Qin1, dq);
+                    P0 = ldexp(P0, dp);
+                    P1 = ldexp(P1, dp);
+                    Qin0 = ldexp(Qin0, dq);
+                    Qin1 = ldexp(Qin1, dq);
 #pragma unroll
-                        for (int n = 2; n <= N; ++n) {
-                            P[n] = sk_ldexp(P[n], dp);
-                            Qin[n] = sk_ldexp(Qin[n], dq);
-                        }
+                    for (int n = 2; n <= N; ++n) {
+                        P[n] = sk_ldexp(P[n], dp);
+                        Qin[n] = sk_ldexp(Qin[n], dq);
                     }
                     E = Ec;
                 }
-                P[0] = (R)P0;
-                P[1] = (R)P1;
-                Qin[0] = (R)Qin0;
-                Qin[1] = (R)Qin1;
-                if (CKPT && (t % S) == 0) {
-                    R* ck = ckb + (int64_t)(t / S) * 2 * (N + 1) * 64;
-#pragma unroll
-                    for (int n = 0; n <= N; ++n) {
-                        ck[n * 64 + r] = P[n];
-                        ck[(N + 1 + n) * 64 + r] = Qin[n];
-                    }
-                    ceb[(int64_t)(t / S) * (SK_LANES + 1) + r] = E;
-                }
-                R Po[N + 1], Qo[N + 1];
-                double Po0, Po1, Qo0, Qo1;
-                int Tc = 0;
-                sk_cell_fwd<R, N, TMAX>(P, Qin, P0, P1, Qin0, Qin1, cb[u], live, a.tab, Po, Qo, Po0,
-                                        Po1, Qo0, Qo1, nullptr, nullptr,
-                                        (CKPT && TMAX > 0) ? &Tc : nullptr);
-                if (CKPT && TMAX > 0) {
-                    // the adjoint's replay folds the same tail rows
-                    tword |= (unsigned)Tc << (8 * (t % S));
-                    if (t % S == S - 1) {
-                        if (r == 0) ceb[(int64_t)(t / S) * (SK_LANES + 1) + SK_LANES] = (int)tword;
-                        tword = 0u;
-                    }
-                }
+            }
+            P[0] = (R)P0;
+            P[1] = (R)P1;
+            Qin[0] = (R)Qin0;
+            Qin[1] = (R)Qin1;
+            if (CKPT && (um % S) == 0) {
+                R* ck = ckb + (int64_t)(t / S) * 2 * (N + 1) * 64;
 #pragma unroll
                 for (int n = 0; n <= N; ++n) {
-                    P[n] = Po[n];
-                    Qs[n] = Qo[n];
+                    ck[n * 64 + r] = P[n];
+                    ck[(N + 1 + n) * 64 + r] = Qin[n];
                 }
-                P0 = Po0;
-                P1 = Po1;
-                Qs0 = Qo0;
-                Qs1 = Qo1;
-                Es = E;
-                if (live) {
-                    if (r == 63 && has_next) {
-                        if (CKPT) {
-                            sk_edge_write<R, N>(ost + u * GXW, Qo0, Qo1, Qo, E);
-                        } else {
-                            unsigned* rec = rout + (int64_t)j * GXW;
-                            unsigned wd[NW];
-                            *reinterpret_cast<double*>(wd) = Qo0;
-                            *reinterpret_cast<double*>(wd + 2) = Qo1;
-#pragma unroll
-                            for (int n = 2; n <= N; ++n)
-                                *reinterpret_cast<R*>(wd + 4 + (n - 2) * (ES / 4)) = Qo[n];
-                            wd[NW - 1] = (unsigned)E;
-                            sk_store_record_coherent<NW>(rec, wd);
-                        }
-                    }
-                    if (i == g.lx - 1 && j == ly - 1) {
-                        R kr = (R)0;
-#pragma unroll
-                        for (int n = N; n >= 2; --n) kr = fma(Po[n] + Qo[n], ifact<R>(n), kr);
-                        const double kv = 0.5 * (Po0 + Qo0 + Po1 + Qo1 + (double)kr);
-                        sk_write_k(a.K, a.Kexp, k_idx, kv, E);
-                    }
+                ceb[(int64_t)(t / S) * (SK_LANES + 1) + r] = E;
+            }
+            R Po[N + 1], Qo[N + 1];
+            double Po0, Po1, Qo0, Qo1;
+            int Tc = 0;
+            sk_cell_fwd<R, N, TMAX, false, true, false, 1, SMALL>(
+                P, Qin, P0, P1, Qin0, Qin1, cu, live, tab, Po, Qo, Po0, Po1, Qo0, Qo1, nullptr,
+                nullptr, (CKPT && TMAX > 0) ? &Tc : nullptr);
+            if (CKPT && TMAX > 0) {
+                // the adjoint's replay folds the same tail rows
+                tword |= (unsigned)Tc << (8 * (um % S));
+                if (um % S == S - 1) {
+                    if (r == 0) ceb[(int64_t)(t / S) * (SK_LANES + 1) + SK_LANES] = (int)tword;
+                    tword = 0u;
                 }
             }
+#pragma unroll
+            for (int n = 0; n <= N; ++n) {
+                P[n] = Po[n];
+                Qs[n] = Qo[n];
+            }
+            P0 = Po0;
+            P1 = Po1;
+            Qs0 = Qo0;
+            Qs1 = Qo1;
+            Es = E;
+            if (live) {
+                if (r == 63 && has_next) {
+                    if (CKPT) {
+                        sk_edge_write<R, N>(ost + u * GXW, Qo0, Qo1, Qo, E);
+                    } else {
+                        unsigned* rec = rout + (int64_t)j * GXW;
+                        unsigned wd[NW];
+                        *reinterpret_cast<double*>(wd) = Qo0;
+                        *reinterpret_cast<double*>(wd + 2) = Qo1;
+#pragma unroll
+                        for (int n = 2; n <= N; ++n)
+                            *reinterpret_cast<R*>(wd + 4 + (n - 2) * (ES / 4)) = Qo[n];
+                        wd[NW - 1] = (unsigned)E;
+                        sk_store_record_coherent<NW>(rec, wd);
+                    }
+                }
+                if (!FAST && i == g.lx - 1 && j == ly - 1) {
+                    R kr = (R)0;
+#pragma unroll
+                    for (int n = N; n >= 2; --n) kr = fma(Po[n] + Qo[n], ifact<R>(n), kr);
+                    const double kv = 0.5 * (Po0 + Qo0 + Po1 + Qo1 + (double)kr);
+                    sk_write_k(a.K, a.Kexp, k_idx, kv, E);
+                }
+            }
+        };
+        for (; ok && t0 < nloc; t0 += 8) {
+            if (s > 0) {
+                const int need = t0 + 16 < ly ? t0 + 16 : ly;
+                ok = sk_wait_count(prog + s - 1, need, seen, a.abort, a.spin_limit);
+                if (!ok) break;
+                sk_gx_stage<GXW, true>(xr, stage, rin, t0 + 8, r, col0);
+            }
+            load_c(cn, t0 + 8);
+            auto steps = [&](auto fastc) SK_INLINE {
+#pragma unroll 1
+                for (int h = 0; h < 8; h += HU) {
+                    R cg[HU];
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) cg[u] = HU == 8 || h == 0 ? cb[u] : cb[8 - HU + u];
+#pragma unroll
+                    for (int u = 0; u < HU; ++u) step(h + u, u, cg[u], fastc);
+                }
+            };
+            if (t0 >= 64 && t0 + 8 < ly) steps(std::true_type{});
+            else steps(std::false_type{});
             // CKPT: lane 63's records of this block (columns t0 + m - 63
             // that exist) to strip s+1's slot and to the adjoint's copy of
             // the boundary edges, in one pass of all lanes (without CKPT lane
             // 63 stores its records as it goes: the pass's registers would
             // cost that kernel a wave per SIMD)
             if (CKPT && has_next) {
+                const int rh = sk_lane_here(r);
 #pragma unroll
                 for (int h = 0; h < XR; ++h) {
-                    const int w = r + 64 * h, m = w / GXW, qw = w - m * GXW, jc = t0 + m - 63;
+                    const int w = rh + 64 * h, m = w / GXW, qw = w - m * GXW, jc = t0 + m - 63;
                     if (w < 8 * GXW && qw < NW && jc >= 0 && jc < ly)
                         sk_store_coherent(rout + (int64_t)jc * GXW + qw, ost[w]);
                 }
@@ -1314,7 +1469,7 @@ __global__ __launch_bounds__(64) void k_sweep_pipe(const PipeArgs<R> a) {
                     constexpr int QR = N + 2;  // N + 1 coefficients and the exponent
 #pragma unroll
                     for (int e0 = 0; e0 < 8 * QR; e0 += 64) {
-                        const int e = e0 + r, m = e / QR, w = e - m * QR, jc = t0 + m - 63;
+                        const int e = e0 + rh, m = e / QR, w = e - m * QR, jc = t0 + m - 63;
                         if (e < 8 * QR && jc >= 0 && jc < ly) {
                             const SkLds<unsigned> rec = ost + m * GXW;
                             const int64_t o = (int64_t)(s + 1) * ly + jc;
@@ -1365,6 +1520,8 @@ __global__ __launch_bounds__(64) void k_sweep_pipe(const PipeArgs<R> a) {
                     Es = E;
                 }
             }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) cb[u] = cn[u];
         }
         if (!ok) {  // a wait gave up: the pair's value is unknown (later
                     // jobs still run: their waits end at once on the flag)
@@ -1398,8 +1555,20 @@ struct AdjArgs {
 // real exponent, so alignment to the larger exponent ignores it.
 #define SK_ZERO_EXP (-(1 << 29))
 
+// Two entry points of the same body: where the register footprint allows it,
+// the compiler is asked to fit two waves per SIMD (the adjoint is latency
+// bound at one); elsewhere forcing it would spill to scratch.  The FP32
+// exchange variant for N = 8 (approximation) spills 6 registers at two waves
+// and is still faster (1024 x 1024 d = 32 Gram, 32 rows: 1021 -> 647 ms).
+template <typename R, int N, int TMAX, bool GX>
+constexpr bool sk_adj_two_waves() {
+    return sizeof(R) == 4 ? (GX ? TMAX == 0 : (TMAX == 0 || N <= 6))
+                          : (TMAX == 0 && N <= 6 && !GX);
+}
+
 template <typename R, int N, int TMAX, int S, bool GX>
 __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
+    SkTabArg<R>& tab = sk_kernarg<AdjArgs<R>>().tab;
     const int r = threadIdx.x;
     const int64_t local = blockIdx.x;
     const SkPairDesc pd = sk_pair(a.src, local);
@@ -1421,7 +1590,7 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
 #pragma unroll
     for (int h = 0; h < (8 * GXW + 63) / 64; ++h) xr[h] = 0u;
     // column lane 63 reads at step tau (rows that are not the last), or -1
-    auto lane63_col = [&](int tau) -> int {
+    auto lane63_col = [&](int tau) SK_INLINE -> int {
         const int L63 = tau - 63;
         if (tau < 0 || L63 < 0) return -1;
         const int s6 = L63 / g.Tp, j6 = L63 - s6 * g.Tp, i6 = s6 * 64 + 63;
@@ -1445,24 +1614,24 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     // longer tail take the slow path below
     constexpr int TR = TMAX > 0 ? SkTailReg<R>::value : 0;
     // Inputs of a checkpoint segment are loaded one segment ahead (PF: the
-    // stride-4 kernels, whose registers allow two waves per SIMD only, so
-    // memory latency is not hidden by other waves): the segment's cell
+    // stride-4 kernels and FP64 (where they fit), whose registers allow one or
+    // two waves per SIMD only, so memory latency is not hidden by other waves): the segment's cell
     // constants at the top of the previous segment, the lane state, its
     // exponent and one word per lane of the boundary edges lane 0 reads at
     // steps 1..S-1 (plus, in lane TWL, the tail-length word) once the
     // previous segment's replay no longer needs its own.  The boundary edges
     // go through LDS, so no load is waited for inside a segment.
-    constexpr bool PF = S >= 4;
+    constexpr bool PF = S >= 4 || (ES == 8 && N <= 8 && (N <= 5 || !sk_adj_two_waves<R, N, TMAX, GX>()));
     constexpr int QW = sk_adj_qst_words(N, ES), TWL = (S - 1) * QW;
     static_assert(!PF || (S <= 4 && TWL < 64), "staged boundary edges exceed one word per lane");
     R pfP[N + 1], pfQ[N + 1], pfc[S];
     int pfE = 0;
     unsigned pfq = 0u;
-    auto prefetch_c = [&](int kk) {
+    auto prefetch_c = [&](int kk) SK_INLINE {
 #pragma unroll
         for (int u = 0; u < S; ++u) pfc[u] = cs[(int64_t)(kk * S + u) * 64 + r];
     };
-    auto prefetch_state = [&](int kk) {
+    auto prefetch_state = [&](int kk) SK_INLINE {
         const R* ck = a.ck + pd.ck_off + (int64_t)kk * 2 * (N + 1) * 64;
 #pragma unroll
         for (int n = 0; n <= N; ++n) {
@@ -1472,8 +1641,9 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
         pfE = sk_ld_nt(a.ce + pd.ce_off + (int64_t)kk * (SK_LANES + 1) + r);
         // word w of the edge lane 0 takes at step u (live, strips >= 1)
         pfq = 0u;
-        if (r < TWL) {
-            const int u = 1 + r / QW, w = r - (u - 1) * QW;
+        const int rh = sk_lane_here(r);
+        if (rh < TWL) {
+            const int u = 1 + rh / QW, w = rh - (u - 1) * QW;
             const int L0 = kk * S + u, s0 = L0 / g.Tp, j0 = L0 - s0 * g.Tp;
             if (s0 >= 1 && s0 < g.nstrips && j0 < g.ly && s0 * 64 < g.lx) {
                 const int64_t o = (int64_t)s0 * g.ly + j0;
@@ -1482,7 +1652,7 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
                 else if (w == QW - 1)
                     pfq = (unsigned)a.qe[pd.qe_off + o];
             }
-        } else if (TMAX > 0 && r == TWL) {
+        } else if (TMAX > 0 && rh == TWL) {
             pfq = (unsigned)a.ce[pd.ce_off + (int64_t)kk * (SK_LANES + 1) + SK_LANES];
         }
     };
@@ -1490,10 +1660,24 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     // state) and the left edge Qin (from lane r-1, or the strip boundary /
     // the initial edge for lane 0), aligned to a common exponent E.  Step 0
     // takes the checkpoint as it is.  Returns whether the cell is live.
+    // FAST segments (the pairs of k_sweep's fast blocks; Tp = 64 too, nothing
+    // is read ahead here): lane r is in column tT + u - r of strip sS, or,
+    // while r > tT + u, in column Tp + tT + u - r of strip sS - 1.  Lane 63 of
+    // the last strip, whose right edge ends the grid, receives zeros from the
+    // lane move, and so does the last row of a partial strip: lanes without a
+    // cell hold zero adjoints from the pair's start, and keep them until their
+    // last cell (c = 0 there, in the steps past the last one too).  A segment
+    // in which lane 0 leaves a strip is general.
+    const bool one_strip = g.nstrips == 1, fastp = one_strip || g.Tp == g.ly;
+    const int Tf = one_strip ? 0x7fffffff : g.Tp;
+    // lane 0's place at the segment's first step
+    int sS = one_strip ? 0 : ((nck - 1) * S) / g.Tp, tT = (nck - 1) * S - sS * g.Tp;
     auto replay_in = [&](int u, R (&P)[N + 1], const R (&Qs)[N + 1], R (&Qin)[N + 1], int& E,
-                         int Es, int L, int s, int j) -> bool {
+                         int Es, int L, int s, int j, auto fastc) SK_INLINE -> bool {
+        constexpr bool FAST = decltype(fastc)::value;
         const int i = s * 64 + r;
-        const bool live = (L >= 0) && (s < g.nstrips) && (j < g.ly) && (i < g.lx);
+        const bool live = FAST || ((L >= 0) && (s < g.nstrips) && (j < g.ly) && (i < g.lx));
+        const int s0 = FAST ? sS : s, j0 = FAST ? tT + u : j;  // lane 0's place
         if (u == 0) {
 #pragma unroll
             for (int n = 0; n <= N; ++n) Qin[n] = Qs[n];
@@ -1502,14 +1686,18 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
 #pragma unroll
         for (int n = 0; n <= N; ++n) Qin[n] = lane_from_prev(Qs[n]);
         int Ein = lane_from_prev(Es);
-        if (live) {
-            if (j == 0) {
+        auto start_row = [&]() SK_INLINE {
 #pragma unroll
-                for (int n = 0; n <= N; ++n) P[n] = n == 0 ? (R)1 : (R)0;
-                E = 0;
-            }
+            for (int n = 0; n <= N; ++n) P[n] = n == 0 ? (R)1 : (R)0;
+            E = 0;
+        };
+        if (FAST && tT < 64) {  // (a branch: see k_sweep)
+            if (sk_lane_here(r) == tT + u) start_row();
+        }
+        if (live) {
+            if (!FAST && j == 0) start_row();
             if (r == 0) {
-                if (s == 0) {
+                if (s0 == 0) {
 #pragma unroll
                     for (int n = 0; n <= N; ++n) Qin[n] = n == 0 ? (R)1 : (R)0;
                     Ein = 0;
@@ -1518,40 +1706,59 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
 #pragma unroll
                     for (int n = 0; n <= N; ++n) Qin[n] = ((SkLds<R>)q)[n];
                     Ein = (int)q[QW - 1];
-                } else {
-                    const int64_t o = (int64_t)s * g.ly + j;
+                } else if (!FAST || s0 < g.nstrips) {
+                    const int64_t o = (int64_t)s0 * g.ly + j0;
 #pragma unroll
                     for (int n = 0; n <= N; ++n) Qin[n] = a.qb[pd.qb_off + o * (N + 1) + n];
                     Ein = a.qe[pd.qe_off + o];
                 }
             }
-            const int Ec = E > Ein ? E : Ein;
-            const int dp = E - Ec, dq = Ein - Ec;
-            if (sk_wave_any(dp != 0 || dq != 0)) {
+            if (sk_wave_any(E != Ein)) {
+                const int Ec = E > Ein ? E : Ein;
+                const int dp = E - Ec, dq = Ein - Ec;
 #pragma unroll
                 for (int n = 0; n <= N; ++n) {
                     P[n] = sk_ldexp(P[n], dp);
                     Qin[n] = sk_ldexp(Qin[n], dq);
                 }
+                E = Ec;
             }
-            E = Ec;
         }
         return live;
+    };
+    // endpoint seed (once per pair): L = gK * 1/2 sum_n (Po'_n + Qo'_n)/n!
+    auto seed_edges = [&](R (&ap)[N + 1], R (&aq)[N + 1], int& ea, int& eb) SK_INLINE {
+        const R g0 = sk_value_here((R)0.5 * gk);
+#pragma unroll
+        for (int n = 0; n <= N; ++n) {
+            ap[n] = g0 * ifact<R>(n);
+            aq[n] = ap[n];
+        }
+        ea = gexp;
+        eb = gexp;
     };
     // One adjoint step (replayed step u of the segment at tau0): the adjoint
     // of the cell's top edge comes from this lane's later cell, that of its
     // right edge from lane r+1 (lane 63: the next strip's lane 0, through the
     // ring or the staging slot); `cell(ap, aq, gv)` maps them to the inputs'
     // adjoints (lp, lqs) and dL/dc.
-    auto adj_step = [&](int u, int tau0, bool live, int ss, int jj, int Eu, auto&& cell) {
+    auto adj_step = [&](int u, int tau0, bool live, int ss, int jj, int Eu, auto&& cell, auto fastc) SK_INLINE {
+        constexpr bool FAST = decltype(fastc)::value;
         const int tau = tau0 + u;
         const int i = ss * 64 + r;
         const bool last_row = (i == g.lx - 1), last_col = (jj == g.ly - 1);
         R lq_recv[N + 1];
 #pragma unroll
         for (int n = 0; n <= N; ++n) lq_recv[n] = lane_from_next(lqs[n]);
-        int El_recv = lane_from_next(Els);
-        if (r == 63 && live && !last_row) {
+        // (FAST: lane 63 of the last strip keeps its own exponent for its zeros)
+        int El_recv = FAST ? lane_from_next_or(Els, El) : lane_from_next(Els);
+        int jr = jj, s63 = sS;
+        if (FAST) {
+            jr = tT + u - 63;
+            s63 = jr < 0 ? sS - 1 : sS;
+            jr = jr < 0 ? jr + g.Tp : jr;
+        }
+        if (r == 63 && (FAST ? (unsigned)s63 < (unsigned)(g.nstrips - 1) : live && !last_row)) {
             if (gx) {
                 const unsigned* rec = stage + (tau & 7) * GXW;
 #pragma unroll
@@ -1560,13 +1767,10 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
                 El_recv = (int)rec[(N + 1) * (ES / 4)];
             } else {
 #pragma unroll
-                for (int n = 0; n <= N; ++n) lq_recv[n] = llds[__mul24(jj, N + 1) + n];
-                El_recv = ltag[jj];
+                for (int n = 0; n <= N; ++n) lq_recv[n] = llds[__mul24(jr, N + 1) + n];
+                El_recv = ltag[jr];
             }
         }
-        // outputs nobody consumes have zero adjoint (a wave-uniform test
-        // skips the selects on steps where every lane consumes both)
-        const bool ta = live && !last_col, tb = live && !last_row;
         R ap[N + 1], aq[N + 1];
 #pragma unroll
         for (int n = 0; n <= N; ++n) {
@@ -1574,53 +1778,66 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
             aq[n] = lq_recv[n];
         }
         int ea = El, eb = El_recv;
-        if (sk_wave_any(!(ta && tb))) {
+        if (FAST) {
+            if (tT < 64) {
+                if (sk_lane_here(r) == tT + u + 1) {  // the last column of strip sS - 1
 #pragma unroll
-            for (int n = 0; n <= N; ++n) {
-                ap[n] = ta ? ap[n] : (R)0;
-                aq[n] = tb ? aq[n] : (R)0;
+                    for (int n = 0; n <= N; ++n) ap[n] = (R)0;
+                    ea = SK_ZERO_EXP;
+                }
             }
-            ea = ta ? ea : SK_ZERO_EXP;
-            eb = tb ? eb : SK_ZERO_EXP;
-        }
-        // endpoint seed (once per pair): L = gK * 1/2 sum_n (Po'_n + Qo'_n)/n!
-        const bool seed = live && last_col && last_row;
-        if (sk_wave_any(seed) && seed) {
+            if (tau == g.nsteps - 1 && r == ((g.lx - 1) & 63)) seed_edges(ap, aq, ea, eb);
+        } else {
+            // outputs nobody consumes have zero adjoint (a wave-uniform test
+            // skips the selects on steps where every lane consumes both)
+            const bool ta = live && !last_col, tb = live && !last_row;
+            if (sk_wave_any(!(ta && tb))) {
 #pragma unroll
-            for (int n = 0; n <= N; ++n) {
-                ap[n] = (R)0.5 * gk * ifact<R>(n);
-                aq[n] = ap[n];
+                for (int n = 0; n <= N; ++n) {
+                    ap[n] = ta ? ap[n] : (R)0;
+                    aq[n] = tb ? aq[n] : (R)0;
+                }
+                ea = ta ? ea : SK_ZERO_EXP;
+                eb = tb ? eb : SK_ZERO_EXP;
             }
-            ea = gexp;
-            eb = gexp;
+            const bool seed = live && last_col && last_row;
+            if (sk_wave_any(seed) && seed) seed_edges(ap, aq, ea, eb);
         }
-        const int Ec = ea > eb ? ea : eb;
-        // vectors tagged SK_ZERO_EXP are zero: only real exponents below
-        // Ec need a shift, which is rare
-        const bool sa = ea != Ec && ea != SK_ZERO_EXP, sb = eb != Ec && eb != SK_ZERO_EXP;
-        if (sk_wave_any(sa || sb)) {
+        int Ec = ea;
+        if (!FAST || sk_wave_any(ea != eb)) {
+            Ec = ea > eb ? ea : eb;
+            // vectors tagged SK_ZERO_EXP are zero: only real exponents below
+            // Ec need a shift, which is rare
+            const bool sa = ea != Ec && ea != SK_ZERO_EXP, sb = eb != Ec && eb != SK_ZERO_EXP;
+            if (sk_wave_any(sa || sb)) {
 #pragma unroll
-            for (int n = 0; n <= N; ++n) {
-                ap[n] = sk_ldexp(ap[n], ea - Ec);
-                aq[n] = sk_ldexp(aq[n], eb - Ec);
+                for (int n = 0; n <= N; ++n) {
+                    ap[n] = sk_ldexp(ap[n], ea - Ec);
+                    aq[n] = sk_ldexp(aq[n], eb - Ec);
+                }
             }
         }
         R gv;
         cell(ap, aq, gv);
         El = Ec;
         Els = Ec;
-        if (live && r == 0 && ss > 0) {
+        if (r == 0 && (FAST ? (unsigned)(sS - 1) < (unsigned)(g.nstrips - 1) : live && ss > 0)) {
+            const int jw = FAST ? tT + u : jj;
             if (gx) {
-                unsigned* rec = xg + (int64_t)jj * GXW;
+                unsigned* rec = xg + (int64_t)jw * GXW;
 #pragma unroll
                 for (int n = 0; n <= N; ++n) *reinterpret_cast<R*>(rec + n * (ES / 4)) = lqs[n];
                 rec[(N + 1) * (ES / 4)] = (unsigned)Ec;
             } else {
 #pragma unroll
-                for (int n = 0; n <= N; ++n) llds[__mul24(jj, N + 1) + n] = lqs[n];
-                ltag[jj] = Ec;
+                for (int n = 0; n <= N; ++n) llds[__mul24(jw, N + 1) + n] = lqs[n];
+                ltag[jw] = Ec;
             }
         }
+        // (general segments wait for the next segment's inputs here: later the
+        // wait, which cannot count the younger operations behind branches,
+        // would drain this step's store)
+        if (PF && !FAST && u == 0) __builtin_amdgcn_s_waitcnt(sk_waitcnt_vm0());
         sk_st_nt(gs + (int64_t)tau * 64 + r, live ? sk_ldexp(gv, Ec + Eu) : (R)0);
         if ((tau & 7) == 0 && live) {
             R m = (R)0;
@@ -1642,20 +1859,17 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
             }
         }
     };
-    if (PF) {
-        prefetch_c(nck - 1);
-        prefetch_state(nck - 1);
-    }
-    for (int kk = nck - 1; kk >= 0; --kk) {
-        const int tau0 = kk * S;
+    int kk = nck - 1, tau0 = kk * S;
+    R cseg[S];
+    int E0 = 0;
+    unsigned tword = 0u;  // tail lengths the forward folded at the segment's steps
+    // the inputs of segment kk; returns its longest tail (wave-uniform)
+    auto segment_in = [&](auto fastc) SK_INLINE -> unsigned {
+        constexpr bool FAST = decltype(fastc)::value;
         // blocks of 8 steps, processed from the top; a segment never
         // straddles two blocks (S divides 8)
         if (gx && (kk == nck - 1 || ((tau0 + S) & 7) == 0))
             sk_gx_stage<GXW>(xr, stage, xg, (tau0 & ~7) - 8, r, lane63_col);
-        const R* ck = a.ck + pd.ck_off + (int64_t)kk * 2 * (N + 1) * 64;
-        R cseg[S];
-        int E0;
-        unsigned tword = 0u;  // tail lengths the forward folded at the segment's steps
         if (PF) {
 #pragma unroll
             for (int u = 0; u < S; ++u) cseg[u] = pfc[u];
@@ -1664,38 +1878,103 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
             // this segment's boundary edges into LDS (the wave's own earlier
             // LDS reads of the previous segment's are ordered before)
             if (r < TWL) qst[r] = pfq;
-            if (kk > 0) prefetch_c(kk - 1);
+            prefetch_c(kk > 0 ? kk - 1 : 0);  // (the last segment's reload is not used)
         } else {
+#pragma unroll
+            for (int u = 0; u < S; ++u) cseg[u] = cs[(int64_t)(tau0 + u) * 64 + r];
             E0 = sk_ld_nt(a.ce + pd.ce_off + (int64_t)kk * (SK_LANES + 1) + r);
             if (TMAX > 0)
                 tword = (unsigned)__builtin_amdgcn_readfirstlane(
                     a.ce[pd.ce_off + (int64_t)kk * (SK_LANES + 1) + SK_LANES]);
         }
-        unsigned tseg = 0u;  // longest tail of the segment (wave-uniform)
+        unsigned tseg = 0u;
 #pragma unroll
         for (int u = 0; u < S; ++u) {
             const unsigned tu = (tword >> (8 * u)) & 0xffu;
             tseg = tu > tseg ? tu : tseg;
         }
-        if (TMAX == 0 || tseg <= (unsigned)TR) {
-            // ---- replay the segment's forward from the checkpoint, recording
-            // each cell's row derivatives, kept tail length and exponent
-            constexpr int M = N + TR;
-            R Dp[S][M], Dq[S][M];
-            R Wst[S][N];  // c^m/m! of each step, kept for its adjoint (PF only)
-            int Tst[S], Est[S];
-            bool lv[S];
-            int sst[S], jst[S];
-            if (!PF) {
+        return tseg;
+    };
+    // ---- replay the segment's forward from the checkpoint, recording
+    // each cell's row derivatives, kept tail length and exponent; then the
+    // adjoint steps in reverse
+    auto segment = [&](auto fastc) SK_INLINE {
+        constexpr bool FAST = decltype(fastc)::value;
+            constexpr int SMALL = FAST && sk_small_path<R, N>() ? SK_SMALL_ASK : SK_SMALL_OFF, M = N + TR;
+        const R* ck = a.ck + pd.ck_off + (int64_t)kk * 2 * (N + 1) * 64;
+        R Dp[S][M], Dq[S][M];
+        R Wst[S][N];  // c^m/m! of each step, kept for its adjoint (PF only)
+        int Tst[S], Est[S];
+        bool lv[S];
+        int sst[S], jst[S];
+        int E = E0;
+        R P[N + 1], Qs[N + 1];
 #pragma unroll
-                for (int u = 0; u < S; ++u) cseg[u] = cs[(int64_t)(tau0 + u) * 64 + r];
-            }
-            int E = E0;
-            R P[N + 1], Qs[N + 1];
+        for (int n = 0; n <= N; ++n) {
+            P[n] = PF ? pfP[n] : sk_ld_nt(ck + n * 64 + r);
+            Qs[n] = PF ? pfQ[n] : sk_ld_nt(ck + (N + 1 + n) * 64 + r);
+        }
+        int Es = E;
+        int L = tau0 - r, s = 0, j = 0;
+        if (!FAST && L >= 0) {
+            s = L / g.Tp;
+            j = L - s * g.Tp;
+        }
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            R Qin[N + 1];
+            const bool live = replay_in(u, P, Qs, Qin, E, Es, L, s, j, fastc);
+            lv[u] = live;
+            sst[u] = s;
+            jst[u] = j;
+            Est[u] = E;
+            R Po[N + 1], Qo[N + 1];
+            double Po0, Po1, Qo0, Qo1;
+            Tst[u] = (int)((tword >> (8 * u)) & 0xffu);
+            sk_cell_fwd<R, N, TR, true, false, true, 1, SMALL>(
+                P, Qin, 0.0, 0.0, 0.0, 0.0, cseg[u], live, tab, Po, Qo, Po0, Po1, Qo0, Qo1, Dp[u],
+                Dq[u], nullptr, Tst[u], PF ? Wst[u] : nullptr);
 #pragma unroll
             for (int n = 0; n <= N; ++n) {
-                P[n] = PF ? pfP[n] : sk_ld_nt(ck + n * 64 + r);
-                Qs[n] = PF ? pfQ[n] : sk_ld_nt(ck + (N + 1 + n) * 64 + r);
+                P[n] = Po[n];
+                Qs[n] = Qo[n];
+            }
+            Es = E;
+            if (!FAST) {
+                if (L >= 0) {
+                    if (++j == g.Tp) {
+                        j = 0;
+                        ++s;
+                    }
+                }
+                ++L;
+            }
+        }
+        // the next segment's state loads while this one's adjoint runs (held
+        // here: the scheduler would sink them to the segment's end)
+        if (PF) prefetch_state(kk > 0 ? kk - 1 : 0);
+        if (PF) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = S - 1; u >= 0; --u)
+            adj_step(u, tau0, lv[u], sst[u], jst[u], Est[u], [&](R (&ap)[N + 1], R (&aq)[N + 1], R& gv) {
+                sk_cell_adj<R, N, TR, 1, SMALL>(cseg[u], Tst[u], tab, ap, aq, Dp[u], Dq[u], lp, lqs,
+                                                 gv, PF ? Wst[u] : nullptr);
+            }, fastc);
+    };
+    // ---- slow path (a tail longer than TR rows in the segment): for each
+    // step u, from the last, replay steps 0..u-1 from the checkpoint to
+    // recover the cell's inputs, then take the adjoint step with the row
+    // derivatives computed from those inputs
+    auto segment_slow = [&]() SK_INLINE {
+        const R* ck = a.ck + pd.ck_off + (int64_t)kk * 2 * (N + 1) * 64;
+#pragma unroll 1
+        for (int u = S - 1; u >= 0; --u) {
+            int E = E0;
+            R P[N + 1], Qs[N + 1], Qin[N + 1];
+#pragma unroll
+            for (int n = 0; n <= N; ++n) {
+                P[n] = ck[n * 64 + r];
+                Qs[n] = ck[(N + 1 + n) * 64 + r];
             }
             int Es = E;
             int L = tau0 - r, s = 0, j = 0;
@@ -1703,21 +1982,17 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
                 s = L / g.Tp;
                 j = L - s * g.Tp;
             }
-#pragma unroll
-            for (int u = 0; u < S; ++u) {
-                R Qin[N + 1];
-                const bool live = replay_in(u, P, Qs, Qin, E, Es, L, s, j);
-                lv[u] = live;
-                sst[u] = s;
-                jst[u] = j;
-                Est[u] = E;
+            bool live = false;
+#pragma unroll 1
+            for (int v = 0;; ++v) {
+                live = replay_in(v, P, Qs, Qin, E, Es, L, s, j, std::false_type{});
+                if (v == u) break;
                 R Po[N + 1], Qo[N + 1];
                 double Po0, Po1, Qo0, Qo1;
-                Tst[u] = (int)((tword >> (8 * u)) & 0xffu);
-                sk_cell_fwd<R, N, TR, true, false, true>(P, Qin, 0.0, 0.0, 0.0, 0.0, cseg[u], live,
-                                                         a.tab, Po, Qo, Po0, Po1, Qo0, Qo1, Dp[u],
-                                                         Dq[u], nullptr, Tst[u],
-                                                         PF ? Wst[u] : nullptr);
+                const int Tv = (int)((tword >> (8 * v)) & 0xffu);
+                sk_cell_fwd<R, N, TMAX, false, false, true>(
+                    P, Qin, 0.0, 0.0, 0.0, 0.0, cs[(int64_t)(tau0 + v) * 64 + r], live, tab,
+                    Po, Qo, Po0, Po1, Qo0, Qo1, nullptr, nullptr, nullptr, Tv);
 #pragma unroll
                 for (int n = 0; n <= N; ++n) {
                     P[n] = Po[n];
@@ -1732,80 +2007,52 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
                 }
                 ++L;
             }
-            // the next segment's state loads while this one's adjoint runs
-            if (PF && kk > 0) prefetch_state(kk - 1);
-            // ---- adjoint steps in reverse
-#pragma unroll
-            for (int u = S - 1; u >= 0; --u)
-                adj_step(u, tau0, lv[u], sst[u], jst[u], Est[u], [&](R (&ap)[N + 1], R (&aq)[N + 1], R& gv) {
-                    sk_cell_adj<R, N, TR>(cseg[u], Tst[u], a.tab, ap, aq, Dp[u], Dq[u], lp, lqs, gv,
-                                          PF ? Wst[u] : nullptr);
-                });
-        } else {
-            // ---- slow path (a tail longer than TR rows in this segment):
-            // for each step u, from the last, replay steps 0..u-1 from the
-            // checkpoint to recover the cell's inputs, then take the adjoint
-            // step with the row derivatives computed from those inputs
-#pragma unroll 1
-            for (int u = S - 1; u >= 0; --u) {
-                int E = E0;
-                R P[N + 1], Qs[N + 1], Qin[N + 1];
-#pragma unroll
-                for (int n = 0; n <= N; ++n) {
-                    P[n] = ck[n * 64 + r];
-                    Qs[n] = ck[(N + 1 + n) * 64 + r];
-                }
-                int Es = E;
-                int L = tau0 - r, s = 0, j = 0;
-                if (L >= 0) {
-                    s = L / g.Tp;
-                    j = L - s * g.Tp;
-                }
-                bool live = false;
-#pragma unroll 1
-                for (int v = 0;; ++v) {
-                    live = replay_in(v, P, Qs, Qin, E, Es, L, s, j);
-                    if (v == u) break;
-                    R Po[N + 1], Qo[N + 1];
-                    double Po0, Po1, Qo0, Qo1;
-                    const int Tv = (int)((tword >> (8 * v)) & 0xffu);
-                    sk_cell_fwd<R, N, TMAX, false, false, true>(
-                        P, Qin, 0.0, 0.0, 0.0, 0.0, cs[(int64_t)(tau0 + v) * 64 + r], live, a.tab,
-                        Po, Qo, Po0, Po1, Qo0, Qo1, nullptr, nullptr, nullptr, Tv);
-#pragma unroll
-                    for (int n = 0; n <= N; ++n) {
-                        P[n] = Po[n];
-                        Qs[n] = Qo[n];
-                    }
-                    Es = E;
-                    if (L >= 0) {
-                        if (++j == g.Tp) {
-                            j = 0;
-                            ++s;
-                        }
-                    }
-                    ++L;
-                }
-                const int Tu = (int)((tword >> (8 * u)) & 0xffu);
-                const R cu = cs[(int64_t)(tau0 + u) * 64 + r];
-                adj_step(u, tau0, live, s, j, E, [&](R (&ap)[N + 1], R (&aq)[N + 1], R& gv) {
-                    sk_cell_adj_in<R, N, TMAX>(cu, Tu, a.tab, ap, aq, P, Qin, lp, lqs, gv);
-                });
-            }
-            if (PF && kk > 0) prefetch_state(kk - 1);
+            const int Tu = (int)((tword >> (8 * u)) & 0xffu);
+            const R cu = cs[(int64_t)(tau0 + u) * 64 + r];
+            adj_step(u, tau0, live, s, j, E, [&](R (&ap)[N + 1], R (&aq)[N + 1], R& gv) {
+                sk_cell_adj_in<R, N, TMAX>(cu, Tu, tab, ap, aq, P, Qin, lp, lqs, gv);
+            }, std::false_type{});
         }
+        if (PF) prefetch_state(kk > 0 ? kk - 1 : 0);
+    };
+    auto advance = [&]() SK_INLINE {
+        --kk;
+        tau0 -= S;
+        for (tT -= S; tT < 0 && sS > 0; tT += g.Tp) --sS;
+    };
+    // (FP64 kernels of one wave per SIMD, bound by their general registers,
+    // gain 2-4% from fast segments at most and go without them)
+    constexpr bool FASTK = ES == 4 || sk_adj_two_waves<R, N, TMAX, GX>();
+    auto fast = [&]() SK_INLINE {  // wave-uniform
+        return fastp && kk >= 0 && tT + S < Tf;
+    };
+    if (PF) {
+        prefetch_c(kk);
+        prefetch_state(kk);
     }
-}
-
-// Two entry points of the same body: where the register footprint allows it,
-// the compiler is asked to fit two waves per SIMD (the adjoint is latency
-// bound at one); elsewhere forcing it would spill to scratch.  The FP32
-// exchange variant for N = 8 (approximation) spills 6 registers at two waves
-// and is still faster (1024 x 1024 d = 32 Gram, 32 rows: 1021 -> 647 ms).
-template <typename R, int N, int TMAX, bool GX>
-constexpr bool sk_adj_two_waves() {
-    return sizeof(R) == 4 ? (GX ? TMAX == 0 : (TMAX == 0 || N <= 6))
-                          : (TMAX == 0 && N <= 6 && !GX);
+    while (kk >= 0) {
+        unsigned tseg = 0u;
+        bool in = false;  // the segment's inputs are taken
+        if constexpr (FASTK) {
+            if (fast()) {
+                // (a loop of their own, entered with nothing in flight, for the
+                // reason given in k_sweep)
+                __builtin_amdgcn_s_waitcnt(sk_waitcnt_vm0());
+                do {
+                    tseg = segment_in(std::true_type{});
+                    in = TMAX > 0 && tseg > (unsigned)TR;
+                    if (in) break;
+                    segment(std::true_type{});
+                    advance();
+                } while (fast());
+                if (!in) continue;
+            }
+        }
+        if (!in) tseg = segment_in(std::false_type{});
+        if (TMAX == 0 || tseg <= (unsigned)TR) segment(std::false_type{});
+        else segment_slow();
+        advance();
+    }
 }
 
 template <typename R, int N, int TMAX, int S, bool GX>
@@ -1874,6 +2121,7 @@ __host__ __device__ constexpr int sk_adj_pipe_lds(int N, int TMAX, int S) {
 
 template <typename R, int N, int TMAX, int S>
 __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
+    SkTabArg<R>& tab = sk_kernarg<AdjPipeArgs<R>>().tab;
     const int r = threadIdx.x;
     constexpr int ES = (int)sizeof(R), GXW = sk_gx_words(N, ES);
     constexpr int TR = TMAX > 0 ? SkTailReg<R>::value : 0;
@@ -1883,11 +2131,9 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
     R* dlds = reinterpret_cast<R*>(sk_smem + sk_gx_stage_bytes(N, ES)) + r;  // [2][S][M][64], this lane's slot
     auto DPu = [&](int u) { return dlds + (0 * S + u) * M * 64; };
     auto DQu = [&](int u) { return dlds + (1 * S + u) * M * 64; };
-    // FP32: lane 0's replayed boundary edges are loaded one segment ahead,
-    // and lane 0's outgoing records leave once per block (FP64 has no
-    // registers to spare for either).  (Loading the segment's lane state one
-    // segment ahead as well costs this kernel a wave per SIMD: 85.8 -> 92.0 ms
-    // on 4096 uneven pairs.)
+    // FP32: the segment's inputs, lane 0's replayed boundary edges among them,
+    // are loaded one segment ahead, and lane 0's outgoing records leave once
+    // per block (FP64 has no registers to spare for either).
     constexpr bool PF = ES == 4;
     constexpr int QW = sk_adj_qst_words(N, ES);
     static_assert(!PF || (S - 1) * QW <= 64, "staged boundary edges exceed one word per lane");
@@ -1915,13 +2161,13 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
         const R gk = a.gK[pd.g_idx];
         const int gexp = a.gKexp ? a.gKexp[pd.g_idx] : 0;
         // column lane 63 reads at local step t, or -1
-        auto col63 = [&](int t) -> int {
+        auto col63 = [&](int t) SK_INLINE -> int {
             const int j = t - 63;
             return (has_next && j >= 0 && j < ly) ? j : -1;
         };
         // count of strip s+1 (columns handed over from the top) that covers
         // the columns of the block of steps b .. b+7
-        auto need_of = [&](int b) -> int {
+        auto need_of = [&](int b) SK_INLINE -> int {
             const int lo = b - 63, hi = b + 7 - 63;
             if (!has_next || hi < 0 || lo >= ly) return 0;
             return ly - (lo < 0 ? 0 : lo);
@@ -1938,10 +2184,11 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
         for (int h = 0; h < XR; ++h) xr[h] = 0u;
         // a checkpoint sweep that gave up left incomplete checkpoints: no replay
         bool ok = __hip_atomic_load(a.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+        int seen = 0;  // last count read of strip s+1
         if (ok) {  // records of the first (topmost) block
             const int nd = need_of(nloc - 8);
             if (nd > 0) {
-                ok = sk_wait_count(prog + s + 1, nd, a.abort, a.spin_limit);
+                ok = sk_wait_count(prog + s + 1, nd, seen, a.abort, a.spin_limit);
                 if (ok) {
 #pragma unroll
                     for (int h = 0; h < XR; ++h) {
@@ -1959,9 +2206,12 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
         }
         // inputs of replayed step u (column j of this lane): as in the
         // batched adjoint, with the strip's own first column and boundary
+        // (FAST: every lane inside the strip, past its first column and before
+        // its last; see k_sweep)
         auto replay_in = [&](int u, int j, R (&P)[N + 1], const R (&Qs)[N + 1], R (&Qin)[N + 1],
-                             int& E, int Es) -> bool {
-            const bool live = rowok && j >= 0 && j < ly;
+                             int& E, int Es, auto fastc) SK_INLINE -> bool {
+            constexpr bool FAST = decltype(fastc)::value;
+            const bool live = FAST || (rowok && j >= 0 && j < ly);
             if (u == 0) {
 #pragma unroll
                 for (int n = 0; n <= N; ++n) Qin[n] = Qs[n];
@@ -1971,7 +2221,7 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
             for (int n = 0; n <= N; ++n) Qin[n] = lane_from_prev(Qs[n]);
             int Ein = lane_from_prev(Es);
             if (live) {
-                if (j == 0) {
+                if (!FAST && j == 0) {
 #pragma unroll
                     for (int n = 0; n <= N; ++n) P[n] = n == 0 ? (R)1 : (R)0;
                     E = 0;
@@ -1993,33 +2243,34 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                         Ein = a.qe[pd.qe_off + o];
                     }
                 }
-                const int Ec = E > Ein ? E : Ein;
-                const int dp = E - Ec, dq = Ein - Ec;
-                if (sk_wave_any(dp != 0 || dq != 0)) {
+                if (sk_wave_any(E != Ein)) {
+                    const int Ec = E > Ein ? E : Ein;
+                    const int dp = E - Ec, dq = Ein - Ec;
 #pragma unroll
                     for (int n = 0; n <= N; ++n) {
                         P[n] = sk_ldexp(P[n], dp);
                         Qin[n] = sk_ldexp(Qin[n], dq);
                     }
+                    E = Ec;
                 }
-                E = Ec;
             }
             return live;
         };
         // one adjoint step at local step t (column jj of this lane)
-        auto adj_step = [&](int t, bool live, int jj, int Eu, auto&& cell) {
+        auto adj_step = [&](int t, bool live, int jj, int Eu, auto&& cell, auto fastc) SK_INLINE {
+            constexpr bool FAST = decltype(fastc)::value;
             const bool last_row = (i == g.lx - 1), last_col = (jj == ly - 1);
             R lq_recv[N + 1];
 #pragma unroll
             for (int n = 0; n <= N; ++n) lq_recv[n] = lane_from_next(lqs[n]);
-            int El_recv = lane_from_next(Els);
-            if (r == 63 && live && !last_row) {  // from strip s+1's lane 0
+            // (FAST: lane 63 of the last strip keeps its own exponent for its zeros)
+            int El_recv = FAST ? lane_from_next_or(Els, El) : lane_from_next(Els);
+            if (r == 63 && (FAST ? has_next : live && !last_row)) {  // from strip s+1's lane 0
                 const unsigned* rec = stage + (t & 7) * GXW;
 #pragma unroll
                 for (int n = 0; n <= N; ++n) lq_recv[n] = *reinterpret_cast<const R*>(rec + n * (ES / 4));
                 El_recv = (int)rec[(N + 1) * (ES / 4)];
             }
-            const bool ta = live && !last_col, tb = live && !last_row;
             R ap[N + 1], aq[N + 1];
 #pragma unroll
             for (int n = 0; n <= N; ++n) {
@@ -2027,32 +2278,39 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                 aq[n] = lq_recv[n];
             }
             int ea = El, eb = El_recv;
-            if (sk_wave_any(!(ta && tb))) {  // selects only on steps that need them
+            if (!FAST) {
+                const bool ta = live && !last_col, tb = live && !last_row;
+                if (sk_wave_any(!(ta && tb))) {  // selects only on steps that need them
 #pragma unroll
-                for (int n = 0; n <= N; ++n) {
-                    ap[n] = ta ? ap[n] : (R)0;
-                    aq[n] = tb ? aq[n] : (R)0;
+                    for (int n = 0; n <= N; ++n) {
+                        ap[n] = ta ? ap[n] : (R)0;
+                        aq[n] = tb ? aq[n] : (R)0;
+                    }
+                    ea = ta ? ea : SK_ZERO_EXP;
+                    eb = tb ? eb : SK_ZERO_EXP;
                 }
-                ea = ta ? ea : SK_ZERO_EXP;
-                eb = tb ? eb : SK_ZERO_EXP;
-            }
-            const bool seed = live && last_col && last_row;
-            if (sk_wave_any(seed) && seed) {
+                const bool seed = live && last_col && last_row;
+                if (sk_wave_any(seed) && seed) {
+                    const R g0 = sk_value_here((R)0.5 * gk);
 #pragma unroll
-                for (int n = 0; n <= N; ++n) {
-                    ap[n] = (R)0.5 * gk * ifact<R>(n);
-                    aq[n] = ap[n];
+                    for (int n = 0; n <= N; ++n) {
+                        ap[n] = g0 * ifact<R>(n);
+                        aq[n] = ap[n];
+                    }
+                    ea = gexp;
+                    eb = gexp;
                 }
-                ea = gexp;
-                eb = gexp;
             }
-            const int Ec = ea > eb ? ea : eb;
-            const bool sa = ea != Ec && ea != SK_ZERO_EXP, sb = eb != Ec && eb != SK_ZERO_EXP;
-            if (sk_wave_any(sa || sb)) {
+            int Ec = ea;
+            if (!FAST || sk_wave_any(ea != eb)) {
+                Ec = ea > eb ? ea : eb;
+                const bool sa = ea != Ec && ea != SK_ZERO_EXP, sb = eb != Ec && eb != SK_ZERO_EXP;
+                if (sk_wave_any(sa || sb)) {
 #pragma unroll
-                for (int n = 0; n <= N; ++n) {
-                    ap[n] = sk_ldexp(ap[n], ea - Ec);
-                    aq[n] = sk_ldexp(aq[n], eb - Ec);
+                    for (int n = 0; n <= N; ++n) {
+                        ap[n] = sk_ldexp(ap[n], ea - Ec);
+                        aq[n] = sk_ldexp(aq[n], eb - Ec);
+                    }
                 }
             }
             R gv;
@@ -2098,10 +2356,11 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
         };
         // word r of the boundary edges lane 0 replays at steps 1..S-1 of
         // segment kk (strips >= 1), loaded one segment ahead of its use
-        auto load_q = [&](int kk) -> unsigned {
+        auto load_q = [&](int kk) SK_INLINE -> unsigned {
             unsigned v = 0u;
-            if (PF && s > 0 && r < (S - 1) * QW) {
-                const int u = 1 + r / QW, w = r - (u - 1) * QW, j = kk * S + u;
+            const int rh = sk_lane_here(r);
+            if (PF && s > 0 && rh < (S - 1) * QW) {
+                const int u = 1 + rh / QW, w = rh - (u - 1) * QW, j = kk * S + u;
                 if (j < ly) {
                     const int64_t o = (int64_t)s * ly + j;
                     if (w < (N + 1) * (ES / 4))
@@ -2113,6 +2372,32 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
             return v;
         };
         unsigned pq = load_q(nckl - 1);
+        // FP32: the segment's cell constants, lane state, exponent and tail
+        // lengths are loaded one segment ahead too (LDS, not registers, bounds
+        // the waves per SIMD here)
+        R pfc[S], pfP[N + 1], pfQ[N + 1];
+        int pfE = 0, pfT = 0;
+        auto load_cseg = [&](int kk) SK_INLINE {
+#pragma unroll
+            for (int u = 0; u < S; ++u) {
+                const int64_t row = (int64_t)kk * S + u;
+                pfc[u] = cs[(row < rows_left ? row : rows_left - 1) * 64 + r];
+            }
+        };
+        auto load_state = [&](int kk) SK_INLINE {
+            const R* ck = ckb + (int64_t)kk * 2 * (N + 1) * 64;
+#pragma unroll
+            for (int n = 0; n <= N; ++n) {
+                pfP[n] = ck[n * 64 + r];
+                pfQ[n] = ck[(N + 1 + n) * 64 + r];
+            }
+            pfE = ceb[(int64_t)kk * (SK_LANES + 1) + r];
+            if (TMAX > 0) pfT = ceb[(int64_t)kk * (SK_LANES + 1) + SK_LANES];
+        };
+        if (PF) {
+            load_cseg(nckl - 1);
+            load_state(nckl - 1);
+        }
         int published = 0;
         for (int kk = nckl - 1; ok && kk >= 0; --kk) {
             const int t0 = kk * S;
@@ -2120,7 +2405,7 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                 const int b = t0 + S - 8;
                 const int nd = need_of(b - 8);
                 if (nd > 0) {
-                    ok = sk_wait_count(prog + s + 1, nd, a.abort, a.spin_limit);
+                    ok = sk_wait_count(prog + s + 1, nd, seen, a.abort, a.spin_limit);
                     if (!ok) break;
                 }
                 sk_gx_stage<GXW, true>(xr, stage, rin, b - 8, r, col63);
@@ -2130,21 +2415,26 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
             if (PF && r < (S - 1) * QW) qst[r] = pq;
             if (PF && kk > 0) pq = load_q(kk - 1);
             const R* ck = ckb + (int64_t)kk * 2 * (N + 1) * 64;
-            const int E0 = ceb[(int64_t)kk * (SK_LANES + 1) + r];
-            const unsigned tword =
-                TMAX > 0 ? (unsigned)__builtin_amdgcn_readfirstlane(ceb[(int64_t)kk * (SK_LANES + 1) + SK_LANES])
-                         : 0u;
+            if (!PF) {
+                load_cseg(kk);
+                pfE = ceb[(int64_t)kk * (SK_LANES + 1) + r];
+                if (TMAX > 0) pfT = ceb[(int64_t)kk * (SK_LANES + 1) + SK_LANES];
+            }
+            const int E0 = pfE;
+            const unsigned tword = TMAX > 0 ? (unsigned)__builtin_amdgcn_readfirstlane(pfT) : 0u;
             unsigned tseg = 0u;  // longest tail of the segment (wave-uniform)
 #pragma unroll
             for (int u = 0; u < S; ++u) {
                 const unsigned tu = (tword >> (8 * u)) & 0xffu;
                 tseg = tu > tseg ? tu : tseg;
             }
-            if (TMAX == 0 || tseg <= (unsigned)TR) {
-                R cseg[S];
+            R cseg[S];
 #pragma unroll
-                for (int u = 0; u < S; ++u)
-                    cseg[u] = (t0 + u < rows_left) ? cs[(int64_t)(t0 + u) * 64 + r] : (R)0;
+            for (int u = 0; u < S; ++u) cseg[u] = pfc[u];
+            if (PF) load_cseg(kk > 0 ? kk - 1 : 0);
+            auto segment = [&](auto fastc, auto smallc) SK_INLINE {
+                constexpr int SMALL = decltype(smallc)::value ? SK_SMALL_ON : SK_SMALL_OFF;
+                constexpr int TRS = SMALL == SK_SMALL_ON ? 0 : TR;
                 // ---- replay the segment's forward from the checkpoint
                 int Tst[S], Est[S], jst[S];
                 bool lv[S];
@@ -2152,24 +2442,24 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                 R P[N + 1], Qs[N + 1];
 #pragma unroll
                 for (int n = 0; n <= N; ++n) {
-                    P[n] = ck[n * 64 + r];
-                    Qs[n] = ck[(N + 1 + n) * 64 + r];
+                    P[n] = PF ? pfP[n] : ck[n * 64 + r];
+                    Qs[n] = PF ? pfQ[n] : ck[(N + 1 + n) * 64 + r];
                 }
                 int Es = E;
 #pragma unroll
                 for (int u = 0; u < S; ++u) {
                     R Qin[N + 1];
                     const int j = t0 + u - r;
-                    const bool live = replay_in(u, j, P, Qs, Qin, E, Es);
+                    const bool live = replay_in(u, j, P, Qs, Qin, E, Es, fastc);
                     lv[u] = live;
                     jst[u] = j;
                     Est[u] = E;
                     R Po[N + 1], Qo[N + 1];
                     double Po0, Po1, Qo0, Qo1;
-                    Tst[u] = (int)((tword >> (8 * u)) & 0xffu);
-                    sk_cell_fwd<R, N, TR, true, false, true, 64>(P, Qin, 0.0, 0.0, 0.0, 0.0, cseg[u],
-                                                                 live, a.tab, Po, Qo, Po0, Po1, Qo0, Qo1,
-                                                                 DPu(u), DQu(u), nullptr, Tst[u]);
+                    Tst[u] = TRS ? (int)((tword >> (8 * u)) & 0xffu) : 0;
+                    sk_cell_fwd<R, N, TRS, true, false, true, 64, SMALL>(
+                        P, Qin, 0.0, 0.0, 0.0, 0.0, cseg[u], live, tab, Po, Qo, Po0, Po1, Qo0, Qo1,
+                        DPu(u), DQu(u), nullptr, Tst[u]);
 #pragma unroll
                     for (int n = 0; n <= N; ++n) {
                         P[n] = Po[n];
@@ -2177,13 +2467,28 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                     }
                     Es = E;
                 }
+                if (PF) {
+                    load_state(kk > 0 ? kk - 1 : 0);
+                    __builtin_amdgcn_sched_barrier(0);  // (held here, as in the batched adjoint)
+                }
                 // ---- adjoint steps in reverse
 #pragma unroll
                 for (int u = S - 1; u >= 0; --u)
                     adj_step(t0 + u, lv[u], jst[u], Est[u], [&](R (&ap)[N + 1], R (&aq)[N + 1], R& gv) {
-                        sk_cell_adj<R, N, TR, 64>(cseg[u], Tst[u], a.tab, ap, aq, DPu(u), DQu(u), lp,
-                                                  lqs, gv);
-                    });
+                        sk_cell_adj<R, N, TRS, 64, SMALL>(cseg[u], Tst[u], tab, ap, aq, DPu(u), DQu(u),
+                                                         lp, lqs, gv);
+                    }, fastc);
+            };
+            if (TMAX == 0 || tseg <= (unsigned)TR) {
+                // (FP64: one kind of segment, its registers are at the limit)
+                constexpr bool SP = sk_small_path<R, N>();
+                using SPt = std::integral_constant<bool, SP>;
+                if (ES == 4 && t0 >= 64 && t0 + S < ly) {
+                    if (SP && tseg == 0 && sk_all_small(cseg)) segment(std::true_type{}, SPt{});
+                    else segment(std::true_type{}, std::false_type{});
+                } else {
+                    segment(std::false_type{}, std::false_type{});
+                }
             } else {
                 // ---- slow path (a tail longer than TR rows in this segment):
                 // replay steps 0..u-1 for each step u, from the last, and take
@@ -2201,14 +2506,14 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                     bool live = false;
 #pragma unroll 1
                     for (int v = 0;; ++v) {
-                        live = replay_in(v, t0 + v - r, P, Qs, Qin, E, Es);
+                        live = replay_in(v, t0 + v - r, P, Qs, Qin, E, Es, std::false_type{});
                         if (v == u) break;
                         R Po[N + 1], Qo[N + 1];
                         double Po0, Po1, Qo0, Qo1;
                         const int Tv = (int)((tword >> (8 * v)) & 0xffu);
                         const R cv = (t0 + v < rows_left) ? cs[(int64_t)(t0 + v) * 64 + r] : (R)0;
                         sk_cell_fwd<R, N, TMAX, false, false, true>(P, Qin, 0.0, 0.0, 0.0, 0.0, cv, live,
-                                                                    a.tab, Po, Qo, Po0, Po1, Qo0, Qo1,
+                                                                    tab, Po, Qo, Po0, Po1, Qo0, Qo1,
                                                                     nullptr, nullptr, nullptr, Tv);
 #pragma unroll
                         for (int n = 0; n <= N; ++n) {
@@ -2220,18 +2525,20 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                     const int Tu = (int)((tword >> (8 * u)) & 0xffu);
                     const R cu = (t0 + u < rows_left) ? cs[(int64_t)(t0 + u) * 64 + r] : (R)0;
                     adj_step(t0 + u, live, t0 + u - r, E, [&](R (&ap)[N + 1], R (&aq)[N + 1], R& gv) {
-                        sk_cell_adj_in<R, N, TMAX>(cu, Tu, a.tab, ap, aq, P, Qin, lp, lqs, gv);
-                    });
+                        sk_cell_adj_in<R, N, TMAX>(cu, Tu, tab, ap, aq, P, Qin, lp, lqs, gv);
+                    }, std::false_type{});
                 }
+                if (PF) load_state(kk > 0 ? kk - 1 : 0);
             }
             // lane 0 has handed over the columns j >= t0: its records of the
             // block's steps t0..t0+7 (column t at step t) go to strip s-1's
             // slot in one pass of all lanes, then the count is published once
             // the stores have completed
             if (s > 0 && (t0 & 7) == 0) {
+                const int rh = sk_lane_here(r);
 #pragma unroll
                 for (int h = 0; h < (PF ? XR : 0); ++h) {
-                    const int w = r + 64 * h, m = w / GXW, qw = w - m * GXW, jc = t0 + m;
+                    const int w = rh + 64 * h, m = w / GXW, qw = w - m * GXW, jc = t0 + m;
                     if (w < 8 * GXW && qw < RW && jc < ly)
                         sk_store_coherent(rout + (int64_t)jc * GXW + qw, ost[w]);
                 }
@@ -2977,6 +3284,7 @@ __device__ __forceinline__ R sk_dot_inc(const R* x, const R* y, int64_t d, int i
 
 template <typename R, int N, int TMAX>
 __global__ __launch_bounds__(256) void k_plain_poly(const PlainArgs<R> a) {
+    SkTabArg<R>& tab = sk_kernarg<PlainArgs<R>>().tab;
     // grid of the lam-order dyadic refinement (lam = 0: the path grid)
     const int lx = a.lx << a.lam, ly = a.ly << a.lam;
     const R sc = (R)1 / (R)((int64_t)1 << (2 * a.lam));
@@ -3000,7 +3308,7 @@ __global__ __launch_bounds__(256) void k_plain_poly(const PlainArgs<R> a) {
             }
             double Po0, Po1, Qo0, Qo1;
             sk_cell_fwd<R, N, TMAX>(P, Q, (double)P[0], (double)P[1], (double)Q[0], (double)Q[1], c,
-                                    true, a.tab, Po, Qo, Po0, Po1, Qo0, Qo1);
+                                    true, tab, Po, Qo, Po0, Po1, Qo0, Qo1);
 #pragma unroll
             for (int n = 0; n <= N; ++n) {
                 pe[i * (N + 1) + n] = Po[n];

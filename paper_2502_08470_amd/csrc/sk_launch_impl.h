@@ -156,8 +156,11 @@ template <typename R> constexpr bool sk_alt_stride() { return sizeof(R) == 4; }
 template <typename R, int N, int TMAX, int S>
 static hipError_t sk_sweep_s(const SweepArgs<R>& a, bool ckpt, int64_t npairs, int ring, bool gx,
                              hipStream_t st) {
-    // exchange launches that checkpoint stage lane 63's records of a block
-    size_t lds = SkLaunch<R>::sweep_lds(N, ring) + (ckpt && gx ? sk_gx_stage_bytes(N, (int)sizeof(R)) : 0);
+    // exchange launches have a staging slot, and with checkpoints stage lane
+    // 63's records of a block; the others only the ring (256 columns at N = 6
+    // in FP32 are 10 KiB: 16 workgroups a CU, four waves per SIMD)
+    const size_t lds = gx ? SkLaunch<R>::sweep_lds(N, ring) + (ckpt ? sk_gx_stage_bytes(N, (int)sizeof(R)) : 0)
+                          : (size_t)ring * sk_ring_col_bytes_fwd(N, (int)sizeof(R));
     dim3 grid((unsigned)npairs), blk(64);
     if (ckpt && gx)
         hipLaunchKernelGGL((k_sweep<R, N, TMAX, true, S, true>), grid, blk, lds, st, a);
