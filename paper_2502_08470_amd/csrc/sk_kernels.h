@@ -12,6 +12,7 @@
 typedef float sk_f4 __attribute__((ext_vector_type(4)));
 typedef double sk_d4 __attribute__((ext_vector_type(4)));
 typedef short sk_s4 __attribute__((ext_vector_type(4)));  // 4 bf16 bit patterns
+typedef short sk_s2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------
 // small utilities
@@ -98,6 +99,17 @@ __device__ __forceinline__ void sk_bf16_split(float x, short& h, short& m, short
     l = (short)(ul >> 16);
 }
 
+// The six products of one 16x16x16 block of split operands (hi, mid, lo),
+// smallest first.
+__device__ __forceinline__ sk_f4 sk_mma_split(const sk_s4 (&a)[3], const sk_s4 (&b)[3], sk_f4 acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[0], b[2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[1], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[0], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[1], b[0], acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[0], b[0], acc, 0, 0, 0);
+}
+
 // One 16x16 tile of the increment Gram, D[m][n] = sum_k a_m[k] b_n[k] over
 // k < dp, where this lane's row pointer `arow` is a_(lane%16) and `brow` is
 // b_(lane%16) (rows flagged not ok read as zero).
@@ -131,12 +143,8 @@ __device__ __forceinline__ typename SkMfma<R>::acc_t sk_gram_tile(const R* arow,
                 sk_bf16_split(bok ? (float)brow[k] : 0.0f, h, m, l);
                 bh[j] = h; bm[j] = m; bl[j] = l;
             }
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bm, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bm, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bh, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, acc, 0, 0, 0);
+            const sk_s4 ap[3] = {ah, am, al}, bp[3] = {bh, bm, bl};
+            acc = sk_mma_split(ap, bp, acc);
         }
     }
     return acc;
@@ -253,6 +261,13 @@ __global__ __launch_bounds__(256) void k_gram_skew(const GramArgs<R> a) {
 // 64-row block kernel reloads 128 y columns and computes a 64 x 128 tile for
 // every 64 rows).  Same tiles and MFMA order as k_gram_skew, so both give
 // identical constants.
+// SPLIT: an increment is split into its BF16 parts once, a column's as it is
+// stored to LDS and a row's as it is loaded to registers, where each wave and
+// tile that read it split it anew; with the rows' parts in registers the parts
+// take no more LDS than the increments did (three workgroups a CU).  The
+// skewed rows leave in 16-byte stores.  2560 pairs of 1024 x 1024 cells,
+// d = 32: 7.35 -> 4.68 ms (their 10.8 GB of constants take 1.6 at the rate of
+// a fill).
 template <typename R, bool SPLIT>
 __global__ __launch_bounds__(256) void k_gram_band(const GramArgs<R> a) {
     const int tid = threadIdx.x;
@@ -268,13 +283,40 @@ __global__ __launch_bounds__(256) void k_gram_band(const GramArgs<R> a) {
     const int tend = tbeg + a.rseg < Tstrip ? tbeg + a.rseg : Tstrip;
     const int dp = a.dpad, ds = dp + 1;  // odd row stride: the 16 rows a tile reads hit distinct banks
     extern __shared__ __align__(16) unsigned char sk_smem[];
-    R* Xs = reinterpret_cast<R*>(sk_smem);  // [64][ds]
+    R* Tt = reinterpret_cast<R*>(sk_smem);  // [2][64][66]: tiles by parity
+    R* Xs = Tt + 2 * 64 * 66;               // [64][ds]
     R* Ys = Xs + 64 * ds;                    // [64][ds]
-    R* Tt = Ys + 64 * ds;                    // [2][64][66]: tiles by parity
+    // SPLIT: the y increments' parts [3][64][ps] instead (8 bytes of padding:
+    // the 16 rows a 4-wide part is read from hit distinct banks), and the
+    // wave's x parts in registers
+    const int ps = dp + 4;
+    short* const Yp = reinterpret_cast<short*>(Xs);
+    constexpr int KB = SPLIT ? 3 : 1;  // blocks of 16 coordinates (dp <= 48)
+    sk_s4 xp[KB][3];
     const R* X = (pd.swap ? a.Y : a.X) + pd.x_off * a.d;
     const R* Y = (pd.swap ? a.X : a.Y) + pd.y_off * a.d;
     const R rscale = (R)1 / (R)(1 << a.lam);
     auto stage_x = [&](int strip) {  // rows 64 strip .. + 63 (refined: segment i >> lam)
+        if constexpr (SPLIT) {
+            const int ir = strip * 64 + 16 * wave + (lane & 15);
+            const bool ok = ir >= 0 && ir < g.lx;
+            const int64_t i = ok ? ir >> a.lam : 0;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = 16 * kb + 4 * (lane >> 4) + j;
+                    float v = 0.0f;
+                    if (ok && k < a.d) v = (X[(i + 1) * a.d + k] - X[i * a.d + k]) * rscale;
+                    short h, m, l;
+                    sk_bf16_split(v, h, m, l);
+                    xp[kb][0][j] = h;
+                    xp[kb][1][j] = m;
+                    xp[kb][2][j] = l;
+                }
+            }
+            return;
+        }
         for (int e = tid; e < 64 * dp; e += 256) {
             const int rr = e / dp, k = e - rr * dp, ir = strip * 64 + rr;
             R v = (R)0;
@@ -288,32 +330,65 @@ __global__ __launch_bounds__(256) void k_gram_band(const GramArgs<R> a) {
     // y increments of virtual columns c0 .. c0 + 63, loaded into registers
     // one tile ahead (their latency overlaps the previous tile) and then
     // stored to LDS; 64 dp / 256 <= 16 values per thread (dp <= 60 here)
-    constexpr int YV = 16;
+    constexpr int YV = 16, YE = SPLIT ? 2 : 1;  // (SPLIT: two neighbouring coordinates at a time)
     R yv[YV];
     auto load_y = [&](int c0) {
 #pragma unroll
-        for (int h = 0; h < YV; ++h) {
-            const int e = tid + 256 * h, cc = e / dp, k = e - cc * dp, vv = c0 + cc;
+        for (int h = 0; h < YV / YE; ++h) {
+            const int e = YE * (tid + 256 * h), cc = e / dp, k0 = e - cc * dp, vv = c0 + cc;
             const int col = vv >= 0 ? vv : g.Tp + vv;
-            yv[h] = (R)0;
-            if (e < 64 * dp && k < a.d && (vv >= 0 || s > 0) && col >= 0 && col < g.ly) {
-                const int j = col >> a.lam;
-                yv[h] = (Y[(int64_t)(j + 1) * a.d + k] - Y[(int64_t)j * a.d + k]) * rscale;
+            const bool ok = e < 64 * dp && (vv >= 0 || s > 0) && col >= 0 && col < g.ly;
+            const int64_t j = ok ? col >> a.lam : 0;
+#pragma unroll
+            for (int q = 0; q < YE; ++q) {
+                const int k = k0 + q;
+                yv[YE * h + q] = (R)0;
+                if (ok && k < a.d) yv[YE * h + q] = (Y[(j + 1) * a.d + k] - Y[j * a.d + k]) * rscale;
             }
         }
     };
     auto store_y = [&]() {
 #pragma unroll
-        for (int h = 0; h < YV; ++h) {
-            const int e = tid + 256 * h, cc = e / dp, k = e - cc * dp;
-            if (e < 64 * dp) Ys[cc * ds + k] = yv[h];
+        for (int h = 0; h < YV / YE; ++h) {
+            const int e = YE * (tid + 256 * h), cc = e / dp, k = e - cc * dp;
+            if (e < 64 * dp) {
+                if constexpr (SPLIT) {
+                    sk_s2 part[3];
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        short hi, mid, lo;
+                        sk_bf16_split(yv[2 * h + q], hi, mid, lo);
+                        part[0][q] = hi;
+                        part[1][q] = mid;
+                        part[2][q] = lo;
+                    }
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) *reinterpret_cast<sk_s2*>(Yp + (64 * p + cc) * ps + k) = part[p];
+                } else {
+                    Ys[cc * ds + k] = yv[h];
+                }
+            }
         }
     };
     auto tile = [&](R* T) {  // T[r][c] = sum_k Xs[r][k] Ys[c][k]; wave w: rows 16w .. 16w+15
 #pragma unroll
         for (int ni = 0; ni < 4; ++ni) {
-            const auto acc = sk_gram_tile<R, SPLIT>(Xs + (16 * wave + (lane & 15)) * ds, true,
-                                                    Ys + (16 * ni + (lane & 15)) * ds, true, dp, lane);
+            typename SkMfma<R>::acc_t acc = {0, 0, 0, 0};
+            if constexpr (SPLIT) {
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) {
+                    if (16 * kb >= dp) break;
+                    sk_s4 yp[3];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        yp[p] = *reinterpret_cast<const sk_s4*>(Yp + (64 * p + 16 * ni + (lane & 15)) * ps +
+                                                                16 * kb + 4 * (lane >> 4));
+                    acc = sk_mma_split(xp[kb], yp, acc);
+                }
+            } else {
+                acc = sk_gram_tile<R, false>(Xs + (16 * wave + (lane & 15)) * ds, true,
+                                             Ys + (16 * ni + (lane & 15)) * ds, true, dp, lane);
+            }
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 T[(16 * wave + SkMfma<R>::row(lane, v)) * 66 + 16 * ni + (lane & 15)] = acc[v];
@@ -332,7 +407,9 @@ __global__ __launch_bounds__(256) void k_gram_band(const GramArgs<R> a) {
         __syncthreads();
         stage_x(s);
     }
-    R* out = a.cskew + pd.c_off + (int64_t)s * g.Tp * 64;
+    R* out = a.cskew + pd.c_off + (int64_t)s * g.Tp * 64;  // (rows of 64 elements of an array aligned to 256 bytes)
+    constexpr int V = 16 / (int)sizeof(R);
+    typedef R vec_t __attribute__((ext_vector_type(V)));
     for (int k = k0; 64 * k < tend; ++k) {
         __syncthreads();  // the previous rows are written: Ys and the older tile are free
         store_y();
@@ -342,12 +419,20 @@ __global__ __launch_bounds__(256) void k_gram_band(const GramArgs<R> a) {
         const R* Tq = Tt + ((k - 1) & 1) * 64 * 66;
         tile(Tc);
         __syncthreads();
+        // 16 bytes a lane (V lanes of one row): its V diagonal elements lie 66 - 1
+        // words apart, so that the lanes of a row and of the next rows hit
+        // distinct banks
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int e = tid + 256 * q, t = 64 * k + (e >> 6), r = e & 63;
+        for (int q = 0; q < 16 / V; ++q) {
+            const int e = V * (tid + 256 * q), t = 64 * k + (e >> 6), r = e & 63;
             if (t < tend) {
-                const int c = t - r - 64 * k;
-                out[(int64_t)t * 64 + r] = c >= 0 ? Tc[r * 66 + c] : Tq[r * 66 + c + 64];
+                vec_t o;
+#pragma unroll
+                for (int h = 0; h < V; ++h) {
+                    const int c = t - r - h - 64 * k;
+                    o[h] = c >= 0 ? Tc[(r + h) * 66 + c] : Tq[(r + h) * 66 + c + 64];
+                }
+                *reinterpret_cast<vec_t*>(out + (int64_t)t * 64 + r) = o;
             }
         }
     }

@@ -109,8 +109,10 @@ hipError_t SkLaunch<R>::gram_band(const GramArgs<R>& a0, int max_strips, int max
     const dim3 grid((unsigned)npairs, (unsigned)max_strips, (unsigned)nseg);
     const size_t lds = gram_band_lds(a.dpad);
     if (a.split) {
+        // (the tiles, and three parts of 2 bytes per increment)
         if constexpr (sizeof(R) == 4)
-            hipLaunchKernelGGL((k_gram_band<R, true>), grid, dim3(256), lds, st, a);
+            hipLaunchKernelGGL((k_gram_band<R, true>), grid, dim3(256),
+                               (size_t)2 * 64 * 66 * sizeof(R) + 3 * 64 * (a.dpad + 4) * sizeof(short), st, a);
         else
             return hipErrorInvalidValue;
     } else {
