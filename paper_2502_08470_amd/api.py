@@ -434,11 +434,24 @@ def _state_budget(device) -> int:
     return int(min(0.5 * free, cap))
 
 
-# Gram calls with fewer pairs than this run paths of several 64-row strips
-# on the strip pipeline: the batched algorithm gives every pair one wave,
-# which leaves most of the GPU's 256 CUs x 4 SIMDs idle (an 8 x 8 Gram of
-# 2049-point paths in R^16: backward 173 ms batched, 17 ms pipelined).
+# The strip pipeline pays while the batched algorithm, which gives every pair
+# one wave, leaves most of the GPU's 256 CUs x 4 SIMDs idle (an 8 x 8 Gram of
+# 2049-point paths in R^16: backward 173 ms batched, 17 ms pipelined).  A strip
+# starts about 170 columns behind the one above it (64 of skew and the
+# hand-over's latency), so shorter rows are done sooner batched: forward /
+# backward of 384 FP32 pairs of order 6, 160 x 130 cells 0.25 / 0.68 ms
+# batched, 0.30 / 0.81 pipelined; 256 x 256 cells 0.60 / 1.62 and 0.46 / 1.23.
+# With more pairs the batched waves fill the GPU first, at a number that grows
+# with the strips a pair has, and sooner in FP64, whose pipelined adjoint has
+# one wave's registers per SIMD only (crossings measured, backward: FP32 about
+# 1250 pairs of 4 strips, FP64 400, 560 and 780 of 4, 6 and 8; 1073 FP64 pairs
+# of 150 x 202 cells 2.65 ms pipelined, 2.28 batched).  Calls of fewer than
+# 64 pairs always take the pipeline (96 x 96 cells: 0.20 / 0.50 ms, batched
+# 0.14 / 0.35).
 PIPELINE_MAX_PAIRS = 2048
+PIPELINE_FEW_PAIRS = 64
+PIPELINE_STRIP_LAG = 170
+PIPELINE_PAIRS_PER_STRIP, PIPELINE_PAIRS_PER_STRIP_F64 = 256, 96
 
 
 def gram_algo(X: torch.Tensor, Y: torch.Tensor, scheme: str = "approx") -> str:
@@ -447,8 +460,13 @@ def gram_algo(X: torch.Tensor, Y: torch.Tensor, scheme: str = "approx") -> str:
     if scheme in ("fd", "fd2"):
         return "batched"
     strips = (X.shape[1] - 2) // 64 + 1 if X.shape[1] > 1 else 0
-    few = X.shape[0] * Y.shape[0] < PIPELINE_MAX_PAIRS
-    return "pipeline" if strips >= 2 and Y.shape[1] > 1 and few else "batched"
+    if strips < 2 or Y.shape[1] <= 1:
+        return "batched"
+    pairs = X.shape[0] * Y.shape[0]
+    most = min(PIPELINE_MAX_PAIRS,
+               strips * (PIPELINE_PAIRS_PER_STRIP_F64 if X.dtype == torch.float64 else PIPELINE_PAIRS_PER_STRIP))
+    few = pairs < PIPELINE_FEW_PAIRS or (Y.shape[1] - 1 > PIPELINE_STRIP_LAG and pairs < most)
+    return "pipeline" if few else "batched"
 
 
 # ---------------------------------------------------------------------------
