@@ -89,7 +89,14 @@ hipError_t SkLaunch<R>::gram_direct(const GramArgs<R>& a, int max_lx, int max_ly
     if (npairs <= 0) return hipSuccess;
     if (a.split || a.dpad > SK_GRAM_DIRECT_DMAX) return hipErrorInvalidValue;
     const size_t lds = gram_direct_lds(a.dpad, max_lx, max_ly);
-    hipLaunchKernelGGL((k_gram_direct<R>), dim3((unsigned)npairs), dim3(256), lds, st, a);
+    const dim3 grid((unsigned)npairs);
+    switch (a.dpad) {  // a multiple of 4
+        case 4: hipLaunchKernelGGL((k_gram_direct<R, 4>), grid, dim3(256), lds, st, a); break;
+        case 8: hipLaunchKernelGGL((k_gram_direct<R, 8>), grid, dim3(256), lds, st, a); break;
+        case 12: hipLaunchKernelGGL((k_gram_direct<R, 12>), grid, dim3(256), lds, st, a); break;
+        case 16: hipLaunchKernelGGL((k_gram_direct<R, 16>), grid, dim3(256), lds, st, a); break;
+        default: return hipErrorInvalidValue;
+    }
     SK_CHECK_LAUNCH();
     return hipSuccess;
 }
