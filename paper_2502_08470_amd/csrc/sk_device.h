@@ -225,12 +225,15 @@ __device__ __forceinline__ bool sk_wave_any(bool v) { return __any(v ? 1 : 0) !=
 // Cells of small |c| in FP32 (orders N >= 5; of N = 4 they would leave out one
 // row and double the code, which short pairs run through cold).  At a step where every lane of
 // the wave has |c| <= SK_SMALL_C = 2^-6, the terms with a factor c^4 or a
-// higher power are below the rounding of the FP32 state and are not formed: the
-// Toeplitz weights stop at w_3 and the Hankel rows at r = 3 (w_4 <= 2^-28.5, and
-// a row's weight in the edge's values is 1/r! <= 1/24, so an edge moves by less
-// than 2^-32 of its largest coefficient, where its own coefficients are
-// rounded to 2^-24; at the |c| of paths of some hundred steps, ten times
-// smaller, by 2^-45).  The interpolation scheme's cell keeps these rows only
+// higher power are below the rounding of the FP32 state and all but one are
+// not formed: the Toeplitz weights stop at w_3 and the Hankel rows at r = 3
+// (w_4 <= 2^-28.5, and a row's weight in the edge's values is 1/r! <= 1/24, so
+// an edge moves by less than 2^-32 of its largest coefficient, where its own
+// coefficients are rounded to 2^-24).  The one that is kept is w_4 times the
+// corner value, into coefficient 4: c^4/24 of one sign in every cell, it adds
+// up over the area of the grid (left out, a Gram of 512 x 512 cells of |c|
+// about 0.003 was 1.0e-7 off instead of 5.6e-8), while the next terms carry a
+// slope of the kernel, small and of either sign.  The interpolation scheme's cell keeps these rows only
 // while its first tail row, from the same weights, is below half of what the
 // tail rule allows (the terms left out of it are below the other half), so it
 // folds no tail row; otherwise it is computed whole.  The adjoint transposes
@@ -440,6 +443,9 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
     } else {
 #pragma unroll
         for (int r = 2; r <= N; ++r) row(r, SK_SMALL_M);
+        const R w4 = w[3] * (c * (R)0.25);
+        Po[4] = fma(w4, P[0], Po[4]);
+        Qo[4] = fma(w4, Q[0], Qo[4]);
     }
     if (Wout) {  // c^m/m!, m = 1..N (SMALL: 1..3), for the adjoint of the same cell
 #pragma unroll
@@ -656,6 +662,9 @@ __device__ __forceinline__ void sk_cell_adj(R c, int T, SkTabArg<R>& tab, const 
     if (!full) {
 #pragma unroll
         for (int r = 1; r <= N; ++r) row(r, SK_SMALL_M);
+        const R w4 = w[3] * (c * (R)0.25);
+        aP[0] = fma(w4, a[4], aP[0]);
+        aQ[0] = fma(w4, b[4], aQ[0]);
     } else {
 #pragma unroll
         for (int m = M0 + 1; m <= N; ++m) w[m] = w[m - 1] * (c * (R)(1.0 / m));
