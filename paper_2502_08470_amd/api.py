@@ -436,22 +436,24 @@ def _state_budget(device) -> int:
 
 # The strip pipeline pays while the batched algorithm, which gives every pair
 # one wave, leaves most of the GPU's 256 CUs x 4 SIMDs idle (an 8 x 8 Gram of
-# 2049-point paths in R^16: backward 173 ms batched, 17 ms pipelined).  A strip
-# starts about 170 columns behind the one above it (64 of skew and the
-# hand-over's latency), so shorter rows are done sooner batched: forward /
-# backward of 384 FP32 pairs of order 6, 160 x 130 cells 0.25 / 0.68 ms
-# batched, 0.30 / 0.81 pipelined; 256 x 256 cells 0.60 / 1.62 and 0.46 / 1.23.
-# With more pairs the batched waves fill the GPU first, at a number that grows
-# with the strips a pair has, and sooner in FP64, whose pipelined adjoint has
-# one wave's registers per SIMD only (crossings measured, backward: FP32 about
-# 1250 pairs of 4 strips, FP64 400, 560 and 780 of 4, 6 and 8; 1073 FP64 pairs
-# of 150 x 202 cells 2.65 ms pipelined, 2.28 batched).  Calls of fewer than
-# 64 pairs always take the pipeline (96 x 96 cells: 0.20 / 0.50 ms, batched
-# 0.14 / 0.35).
+# 2049-point paths in R^16: backward 173 ms batched, 17 ms pipelined).  Times
+# of both, in units of one batched pair's strips x columns steps, P = pairs per
+# SIMD (fitted to backwards of 4 to 2048 pairs, 2 to 16 strips, 96 to 1500
+# columns; the forward's lines lie close by):
+#   batched: waves of one SIMD share it well in FP32, 1 + P / 4; in FP64 the
+#     adjoint keeps one wave per SIMD, 1 + 0.55 P^2 up to P = 1, then 1.45 P;
+#   pipelined: its depth, a strip starting about 150 columns behind the one
+#     above it, or once the GPU is full 0.6 of the depth and the strips' own
+#     steps (columns + 63 of skew each), which FP64 runs at half FP32's rate.
+# Forward / backward in ms: 384 FP32 pairs of order 6, 160 x 130 cells 0.25 /
+# 0.68 batched, 0.30 / 0.81 pipelined; 256 x 256 cells 0.60 / 1.62 and 0.46 /
+# 1.23, of 2048 pairs 0.73 / 2.23 and 0.81 / 2.85.  Backward, 600 pairs of
+# 120 x 1500 cells: FP32 3.59 batched, 2.63 pipelined, FP64 5.66 and 4.71; 1600
+# FP64 pairs of 300 x 100 1.83 and 2.73; training step of 1073 FP64 pairs of
+# 150 x 202 cells 2.28 and 2.65.  Calls of fewer than 64 pairs always take the
+# pipeline (96 x 96 cells: 0.20 / 0.50, batched 0.14 / 0.35).
 PIPELINE_MAX_PAIRS = 2048
 PIPELINE_FEW_PAIRS = 64
-PIPELINE_STRIP_LAG = 170
-PIPELINE_PAIRS_PER_STRIP, PIPELINE_PAIRS_PER_STRIP_F64 = 256, 96
 
 
 def gram_algo(X: torch.Tensor, Y: torch.Tensor, scheme: str = "approx") -> str:
@@ -460,13 +462,17 @@ def gram_algo(X: torch.Tensor, Y: torch.Tensor, scheme: str = "approx") -> str:
     if scheme in ("fd", "fd2"):
         return "batched"
     strips = (X.shape[1] - 2) // 64 + 1 if X.shape[1] > 1 else 0
-    if strips < 2 or Y.shape[1] <= 1:
+    pairs, cols = X.shape[0] * Y.shape[0], Y.shape[1] - 1
+    if strips < 2 or cols < 1 or pairs >= PIPELINE_MAX_PAIRS:
         return "batched"
-    pairs = X.shape[0] * Y.shape[0]
-    most = min(PIPELINE_MAX_PAIRS,
-               strips * (PIPELINE_PAIRS_PER_STRIP_F64 if X.dtype == torch.float64 else PIPELINE_PAIRS_PER_STRIP))
-    few = pairs < PIPELINE_FEW_PAIRS or (Y.shape[1] - 1 > PIPELINE_STRIP_LAG and pairs < most)
-    return "pipeline" if few else "batched"
+    if pairs < PIPELINE_FEW_PAIRS:
+        return "pipeline"
+    f64 = X.dtype == torch.float64
+    per_simd = pairs / 1024
+    batched = 1 + 0.25 * per_simd if not f64 else max(1 + 0.55 * min(per_simd, 1) ** 2, 1.45 * per_simd + 0.1)
+    depth = (cols + 63 + 150 * (strips - 1)) / (strips * cols)
+    pipelined = max(depth, 0.6 * depth + (1.06 if f64 else 0.58) * per_simd * (cols + 63) / cols)
+    return "pipeline" if pipelined < batched else "batched"
 
 
 # ---------------------------------------------------------------------------
