@@ -223,9 +223,9 @@ template <> struct SkEps<double> { static constexpr double value = 1.0 / (double
 __device__ __forceinline__ bool sk_wave_any(bool v) { return __any(v ? 1 : 0) != 0; }
 
 // Cells of small |c| in FP32 (orders N >= 5; of N = 4 they would leave out one
-// row and double the code, which short pairs run through cold).  At a step where every lane of
-// the wave has |c| <= SK_SMALL_C = 2^-6, the terms with a factor c^4 or a
-// higher power are below the rounding of the FP32 state and all but one are
+// row and double the code, which short pairs run through cold).  At a step
+// where every lane of the wave has |c| <= SK_SMALL_C = 2^-6, the terms with a
+// factor c^4 or a higher power are below the rounding of the FP32 state and all but one are
 // not formed: the Toeplitz weights stop at w_3 and the Hankel rows at r = 3
 // (w_4 <= 2^-28.5, and a row's weight in the edge's values is 1/r! <= 1/24, so
 // an edge moves by less than 2^-32 of its largest coefficient, where its own
@@ -233,9 +233,9 @@ __device__ __forceinline__ bool sk_wave_any(bool v) { return __any(v ? 1 : 0) !=
 // corner value, into coefficient 4: c^4/24 of one sign in every cell, it adds
 // up over the area of the grid (left out, a Gram of 512 x 512 cells of |c|
 // about 0.003 was 1.0e-7 off instead of 5.6e-8), while the next terms carry a
-// slope of the kernel, small and of either sign.  The interpolation scheme's cell keeps these rows only
-// while its first tail row, from the same weights, is below half of what the
-// tail rule allows (the terms left out of it are below the other half), so it
+// slope of the kernel, small and of either sign.  The interpolation scheme's
+// cell keeps these rows only while its first tail row, from the same weights,
+// is below half of what the tail rule allows (the terms left out of it are below the other half), so it
 // folds no tail row; otherwise it is computed whole.  The adjoint transposes
 // the same terms.  The test is wave-uniform, once a step (in the pipelined
 // adjoint once a checkpoint segment); the rows it saves are 40% of the

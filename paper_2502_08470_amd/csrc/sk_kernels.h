@@ -961,15 +961,18 @@ void k_sweep(const SweepArgs<R> a) {
     // FAST blocks: pairs whose strips follow each other without idle columns
     // (Tp = ly, and more than 64 columns, so that the entry lane 0 reads one
     // step ahead has been written), or of one strip.  There lane r is in column
-    // tT - r of strip sS, or, while r > tT, in column Tp + tT - r of strip
-    // sS - 1, (sS, tT) lane 0's place at the step, and the lanes' places, their tests and the selects of a
-    // lane that starts a row come down to one comparison in the blocks in
-    // which lanes enter a strip.  Lanes without a cell (before their first,
-    // after their last, past the pair's last row) have c = 0 and compute
-    // values that no cell reads.  Lane 0's edge of the next step is read from
-    // LDS one step ahead, and cells of small |c| take their shorter rows
-    // (SK_SMALL_C; where strips of several are all filled, as in the strip
-    // pipeline, whose values are the same to the last bit while no |c| is small).
+    // tT - r of lane 0's strip, or, while r > tT, in column Tp + tT - r of the
+    // strip before, and the lanes' places, their tests and the selects of a
+    // lane that starts a row come down to one comparison in the blocks in which
+    // lanes enter a strip.  Lanes without a cell (before their first, after
+    // their last, past the pair's last row) have c = 0 and compute values that
+    // no cell reads.  Lane 0's edge of the next step is read from LDS one step
+    // ahead, and cells of small |c| take their shorter rows (SK_SMALL_C; where
+    // strips of several are all filled, as in the strip pipeline, whose values
+    // are the same to the last bit while no |c| is small).  The sweep is bound
+    // by vector instructions: 128 x 128 FP32 pairs of 256 x 256 cells, N = 6:
+    // 7.8 -> 3.9 ms, with checkpoints 7.9 -> 5.3; 64 FP64 pairs of 64 x 64, by
+    // the depth of one wave, 51 -> 42 us.
     const bool one_strip = g.nstrips == 1;  // no boundary edges: lane 0 starts from the initial edge
     const bool fastp = one_strip || (g.Tp == g.ly && g.ly > 64);
     const int Tf = one_strip ? 0x7fffffff : g.Tp;
@@ -1736,7 +1739,11 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     // steps 1..S-1 (plus, in lane TWL, the tail-length word) once the
     // previous segment's replay no longer needs its own.  The boundary edges
     // go through LDS, so no load is waited for inside a segment.
-    constexpr bool PF = S >= 4 || (ES == 8 && N <= 8 && (N <= 5 || !sk_adj_two_waves<R, N, TMAX, GX>()));
+    // (FP64 approximation, N = 7 and the exchange at N <= 4: the prefetched
+    // state would cost a wave per SIMD; 4096 pairs of 1000 x 20 cells, N = 7:
+    // 7.4 ms prefetched, 6.0 not)
+    constexpr bool PF64 = N <= 8 && (TMAX > 0 || (sk_adj_two_waves<R, N, TMAX, GX>() ? N <= 5 : N >= 5 && N != 7));
+    constexpr bool PF = S >= 4 || (ES == 8 && PF64);
     constexpr int QW = sk_adj_qst_words(N, ES), TWL = (S - 1) * QW;
     static_assert(!PF || (S <= 4 && TWL < 64), "staged boundary edges exceed one word per lane");
     R pfP[N + 1], pfQ[N + 1], pfc[S];
@@ -1782,7 +1789,9 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     // lane move, and so does the last row of a partial strip: lanes without a
     // cell hold zero adjoints from the pair's start, and keep them until their
     // last cell (c = 0 there, in the steps past the last one too).  A segment
-    // in which lane 0 leaves a strip is general.
+    // in which lane 0 leaves a strip is general.  (128 x 128 FP32 pairs of
+    // 256 x 256 cells, N = 6: 12.2 -> 9.5 ms; 2560 of 1024 x 1024, N = 8: 57.2
+    // -> 36.9.)
     const bool one_strip = g.nstrips == 1, fastp = one_strip || g.Tp == g.ly;
     const int Tf = one_strip ? 0x7fffffff : g.Tp;
     // lane 0's place at the segment's first step
@@ -3322,10 +3331,7 @@ struct FdArgs {
 // The constants of a block of 8 steps are loaded one block ahead, which leaves
 // the kernel bound by its stream of constants instead of a load's latency in
 // every step; whole blocks of pairs without idle columns do without the lanes'
-// places (see k_sweep).  A node is its left neighbour plus a small change, so
-// that it is rounded once at its own size (as the sum of three neighbours it
-// was rounded three times: 2e-3 instead of 2e-5 off after 510 x 510 cells of
-// the second-order scheme).  64 x 64 FP32 pairs of 256 x 256 refined cells:
+// places (see k_sweep).  64 x 64 FP32 pairs of 256 x 256 refined cells:
 // 1.12 -> 0.33 ms.
 template <typename R>
 __global__ __launch_bounds__(64) void k_sweep_fd(const FdArgs<R> a) {
@@ -3349,10 +3355,8 @@ __global__ __launch_bounds__(64) void k_sweep_fd(const FdArgs<R> a) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) cb[u] = cs[u * 64 + r];
     auto update = [&](R c, R b, R kij) SK_INLINE {
-        const R sum = kown + b;
-        R dk = fma((R)0.5 * c, sum, b - kij);
-        if (a.second) dk = fma(c * c * (R)(1.0 / 12.0), sum + kij, dk);
-        out = kown + dk;
+        out = kown + b - kij + (R)0.5 * c * (kown + b);
+        if (a.second) out = fma(c * c * (R)(1.0 / 12.0), kown + b + kij, out);
         kown = out;
         bprev = b;
     };
