@@ -426,15 +426,27 @@ SkPairSizes add(const SkPairSizes& a, const SkPairSizes& b) {
     return o;
 }
 
+// Bytes a pair adds to a Gram chunk's layout, without the arrays' padding.
+int64_t unpadded_pair(const SkPairSizes& z, size_t es, bool backward) {
+    const int64_t fwd = z.c * (int64_t)es + (z.xb + z.pg) * 4;
+    return !backward ? fwd
+                     : fwd + (z.c + z.cu + z.ck + z.qb + z.dx + z.dy + 1) * (int64_t)es + (z.ce + z.qe + 1) * 4;
+}
+
 // Gram: largest chunk of uniform pairs that fits in `bytes`.
 int64_t gram_chunk(const SkPairSizes& per, int64_t npairs, size_t es, bool backward,
                    size_t bytes, int N) {
     if (npairs <= 0) return 0;
+    bytes = std::min<size_t>(bytes, INT64_MAX / 2);
     // (one pair's layout carries every array's padding, so bytes / one would
     // miss that the whole call fits: a workspace sized for it then ran a
     // second chunk of a few pairs, a whole pair's depth, 0.6 of 6.5 ms on a
-    // 128 x 128 Gram of 256-step paths)
-    if ((size_t)layout_for(scale(per, npairs), npairs, es, backward, false, N).total <= bytes) return npairs;
+    // 128 x 128 Gram of 256-step paths.  The unpadded size is asked first: all
+    // pairs' sizes are multiplied out only where they cannot overflow)
+    const int64_t raw = std::max<int64_t>(1, unpadded_pair(per, es, backward));
+    if (npairs <= (int64_t)(bytes / (size_t)raw) &&
+        (size_t)layout_for(scale(per, npairs), npairs, es, backward, false, N).total <= bytes)
+        return npairs;
     int64_t one = layout_for(per, 1, es, backward, false, N).total;
     if ((size_t)one > bytes) return 0;
     int64_t P = std::min<int64_t>(npairs, (int64_t)(bytes / (size_t)std::max<int64_t>(1, one)) + 1);
