@@ -77,6 +77,14 @@ __host__ __device__ constexpr int sk_waitcnt_vm0() { return 0x0f70; }
 // generic pointer's would be 64-bit with an unused high half.
 template <typename T> using SkLds = __attribute__((address_space(3))) T*;
 
+// Words of the strip-boundary records: rings, staging slots and exchange
+// records hold FP64 and FP32 values and exponents, which one lane writes and
+// another reads at other widths.  Such words are written through these types,
+// which alias every other: through plain ones the compiler may move a read
+// before the write that it depends on.
+typedef unsigned __attribute__((may_alias)) sk_word;
+typedef unsigned long long __attribute__((may_alias)) sk_word2;
+
 // Kernel-argument tables of the interpolation scheme.
 template <typename R>
 struct SkTab {
@@ -117,22 +125,18 @@ __device__ __forceinline__ float lane_from_prev(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
 }
 __device__ __forceinline__ double lane_from_prev(double v) {
-    int2 b = *reinterpret_cast<int2*>(&v);
-    int2 o;
-    o.x = __builtin_amdgcn_update_dpp(0, b.x, 0x138, 0xf, 0xf, true);
-    o.y = __builtin_amdgcn_update_dpp(0, b.y, 0x138, 0xf, 0xf, true);
-    return *reinterpret_cast<double*>(&o);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
 }
 // lane r receives the value of lane r+1 (lane 63 receives 0)
 __device__ __forceinline__ float lane_from_next(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 __device__ __forceinline__ double lane_from_next(double v) {
-    int2 b = *reinterpret_cast<int2*>(&v);
-    int2 o;
-    o.x = __builtin_amdgcn_update_dpp(0, b.x, 0x130, 0xf, 0xf, true);
-    o.y = __builtin_amdgcn_update_dpp(0, b.y, 0x130, 0xf, 0xf, true);
-    return *reinterpret_cast<double*>(&o);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
 }
 
 __device__ __forceinline__ int lane_from_prev(int v) {
@@ -146,12 +150,9 @@ __device__ __forceinline__ float lane_from_prev_or(float v, float lane0) {
         __builtin_amdgcn_update_dpp(__float_as_int(lane0), __float_as_int(v), 0x138, 0xf, 0xf, false));
 }
 __device__ __forceinline__ double lane_from_prev_or(double v, double lane0) {
-    int2 b = *reinterpret_cast<int2*>(&v);
-    int2 z = *reinterpret_cast<int2*>(&lane0);
-    int2 o;
-    o.x = __builtin_amdgcn_update_dpp(z.x, b.x, 0x138, 0xf, 0xf, false);
-    o.y = __builtin_amdgcn_update_dpp(z.y, b.y, 0x138, 0xf, 0xf, false);
-    return *reinterpret_cast<double*>(&o);
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(lane0), __double2loint(v), 0x138, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(lane0), __double2hiint(v), 0x138, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ int lane_from_prev_or(int v, int lane0) {
     return __builtin_amdgcn_update_dpp(lane0, v, 0x138, 0xf, 0xf, false);

@@ -790,8 +790,8 @@ __device__ __forceinline__ int sk_lane_here(int r) { return sk_value_here(r); }
 // COHERENT: the records come from other workgroups (strip pipeline) and are
 // read with device-coherent loads.
 template <int W, bool COHERENT = false, typename F>
-__device__ __forceinline__ void sk_gx_stage(unsigned (&xr)[(8 * W + 63) / 64], unsigned* stage,
-                                            const unsigned* xg, int t_next, int lane, F want) {
+__device__ __forceinline__ void sk_gx_stage(unsigned (&xr)[(8 * W + 63) / 64], sk_word* stage,
+                                            const sk_word* xg, int t_next, int lane, F want) {
     const int r = sk_lane_here(lane);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
 #pragma unroll
@@ -813,6 +813,13 @@ __device__ __forceinline__ void sk_gx_stage(unsigned (&xr)[(8 * W + 63) / 64], u
     }
 }
 
+// the words of a value, for a record
+__device__ __forceinline__ void sk_put_words(unsigned* w, float v) { w[0] = __float_as_uint(v); }
+__device__ __forceinline__ void sk_put_words(unsigned* w, double v) {
+    w[0] = (unsigned)__double2loint(v);
+    w[1] = (unsigned)__double2hiint(v);
+}
+
 template <typename R>
 __device__ __forceinline__ void sk_write_k(R* K, int32_t* Kexp, int64_t idx, double v, int E) {
     if (Kexp) {
@@ -828,13 +835,13 @@ __device__ __forceinline__ void sk_write_k(R* K, int32_t* Kexp, int64_t idx, dou
 // staged exchange record, 8-byte aligned): FP64 coefficients 0 and 1 in
 // words 0..3, coefficients 2..N from word 4, then the exponent.
 template <typename R, int N>
-__device__ __forceinline__ void sk_edge_read(SkLds<unsigned> rec, double& q0, double& q1,
+__device__ __forceinline__ void sk_edge_read(SkLds<sk_word> rec, double& q0, double& q1,
                                              R (&q)[N + 1], int& e) {
     constexpr int ES = (int)sizeof(R), NW = 4 + (N - 1) * ES / 4 + 1, NW2 = (NW + 1) / 2;
     unsigned wv[2 * NW2];
 #pragma unroll
     for (int k = 0; k < NW2; ++k) {
-        const unsigned long long v = ((SkLds<unsigned long long>)rec)[k];
+        const unsigned long long v = ((SkLds<sk_word2>)rec)[k];
         wv[2 * k] = (unsigned)v;
         wv[2 * k + 1] = (unsigned)(v >> 32);
     }
@@ -850,7 +857,7 @@ __device__ __forceinline__ void sk_edge_read(SkLds<unsigned> rec, double& q0, do
     e = (int)wv[NW - 1];
 }
 template <typename R, int N>
-__device__ __forceinline__ void sk_edge_write(SkLds<unsigned> rec, double q0, double q1,
+__device__ __forceinline__ void sk_edge_write(SkLds<sk_word> rec, double q0, double q1,
                                               const R (&q)[N + 1], int e) {
     constexpr int ES = (int)sizeof(R), NW = 4 + (N - 1) * ES / 4 + 1, NW2 = (NW + 1) / 2;
     unsigned wv[2 * NW2];
@@ -871,7 +878,7 @@ __device__ __forceinline__ void sk_edge_write(SkLds<unsigned> rec, double q0, do
     if (NW < 2 * NW2) wv[2 * NW2 - 1] = 0u;
 #pragma unroll
     for (int k = 0; k < NW2; ++k)
-        ((SkLds<unsigned long long>)rec)[k] = (unsigned long long)wv[2 * k] | ((unsigned long long)wv[2 * k + 1] << 32);
+        ((SkLds<sk_word2>)rec)[k] = (unsigned long long)wv[2 * k] | ((unsigned long long)wv[2 * k + 1] << 32);
 }
 
 // Magnitude bookkeeping: every lane carries its own power-of-two exponent E
@@ -905,7 +912,7 @@ void k_sweep(const SweepArgs<R> a) {
     constexpr int ES = (int)sizeof(R), GXW = sk_gx_words(N, ES);
     const bool gx = GX && g.ly > a.gx_cols;  // wave-uniform
     extern __shared__ __align__(16) unsigned char sk_smem[];
-    unsigned* stage = reinterpret_cast<unsigned*>(sk_smem);                // [8][GXW]
+    sk_word* stage = reinterpret_cast<sk_word*>(sk_smem);                // [8][GXW]
     // ring entry of a column: FP64 coefficients 0 and 1, coefficients 2..N,
     // exponent (the layout of a global exchange record), 8-byte aligned
     constexpr int RW = sk_ring_col_bytes_fwd(N, ES) / 4;
@@ -914,9 +921,9 @@ void k_sweep(const SweepArgs<R> a) {
     // adjoint's copy of the boundary edges
     constexpr int OST = (GX && CKPT) ? sk_gx_stage_bytes(N, ES) : 0;
     constexpr int STG = GX ? sk_gx_stage_bytes(N, ES) : 0;  // (no staging slot without the exchange)
-    const SkLds<unsigned> ost = (SkLds<unsigned>)(sk_smem + STG);
-    const SkLds<unsigned> ring = (SkLds<unsigned>)(sk_smem + STG + OST);  // [ly][RW]
-    unsigned* xg = a.xb + pd.xb_off;  // [ly][GXW] (exchange pairs only)
+    const SkLds<sk_word> ost = (SkLds<sk_word>)(sk_smem + STG);
+    const SkLds<sk_word> ring = (SkLds<sk_word>)(sk_smem + STG + OST);  // [ly][RW]
+    sk_word* xg = a.xb + pd.xb_off;  // [ly][GXW] (exchange pairs only)
     unsigned xr[(8 * GXW + 63) / 64];
 #pragma unroll
     for (int h = 0; h < (8 * GXW + 63) / 64; ++h) xr[h] = 0u;
@@ -943,7 +950,7 @@ void k_sweep(const SweepArgs<R> a) {
     // initial edge by a wave-uniform test instead.)
     if (!gx) {
         for (int col = r; col < g.ly; col += 64) {
-            SkLds<unsigned> e = ring + __mul24(col, RW);
+            SkLds<sk_word> e = ring + __mul24(col, RW);
 #pragma unroll
             for (int w = 0; w < RW; ++w) e[w] = (w == 1) ? 0x3ff00000u : 0u;  // words 0-1: 1.0
         }
@@ -1005,7 +1012,7 @@ void k_sweep(const SweepArgs<R> a) {
             for (int n = 2; n <= N; ++n) Bq[n] = (R)0;
             Be = 0;
         } else {
-            sk_edge_read<R, N>(gx ? (SkLds<unsigned>)stage + u * GXW : ring + __mul24(col, RW), B0, B1, Bq, Be);
+            sk_edge_read<R, N>(gx ? (SkLds<sk_word>)stage + u * GXW : ring + __mul24(col, RW), B0, B1, Bq, Be);
         }
     };
     // Step u of the block (um: among the steps unrolled together).
@@ -1195,7 +1202,7 @@ void k_sweep(const SweepArgs<R> a) {
                 }
                 if (e < 8 * QR && (FAST ? (unsigned)(Le - back) < handed
                                         : Le - back >= 0 && sc + 1 < g.nstrips && jc < g.ly)) {
-                    const SkLds<unsigned> rec = gx ? ost + u * GXW : ring + __mul24(jc, RW);
+                    const SkLds<sk_word> rec = gx ? ost + u * GXW : ring + __mul24(jc, RW);
                     const int64_t o = FAST ? (int64_t)(Le - back) + g.ly : (int64_t)(sc + 1) * g.ly + jc;
                     if (w <= N) {
                         R v;
@@ -1366,10 +1373,10 @@ void k_sweep_pipe(const PipeArgs<R> a) {
     constexpr int ES = (int)sizeof(R), GXW = sk_gx_words(N, ES);
     constexpr int XR = (8 * GXW + 63) / 64;
     extern __shared__ __align__(16) unsigned char sk_smem[];
-    unsigned* stage = reinterpret_cast<unsigned*>(sk_smem);  // [8][GXW]
+    sk_word* stage = reinterpret_cast<sk_word*>(sk_smem);  // [8][GXW]
     // lane 63's records of the current 8-step block, stored to the global
     // slot by all lanes at the block's end (before it is published)
-    const SkLds<unsigned> ost = (SkLds<unsigned>)(sk_smem + sk_gx_stage_bytes(N, ES));  // [8][GXW]
+    const SkLds<sk_word> ost = (SkLds<sk_word>)(sk_smem + sk_gx_stage_bytes(N, ES));  // [8][GXW]
     constexpr int NW = 4 + (N - 1) * (ES / 4) + 1;  // words of a record
     constexpr int HU = TMAX == 0 ? 8 : 4;  // steps unrolled together (as in k_sweep)
     for (int64_t q = blockIdx.x; q < a.njobs; q += gridDim.x) {
@@ -1389,7 +1396,7 @@ void k_sweep_pipe(const PipeArgs<R> a) {
         const int i = s * 64 + r;
         const bool rowok = i < g.lx;
         const bool has_next = s + 1 < g.nstrips;
-        const unsigned* rin = xbase + (size_t)((s + 1) & 1) * ly * GXW;  // strip s-1's slot
+        const sk_word* rin = xbase + (size_t)((s + 1) & 1) * ly * GXW;  // strip s-1's slot
         unsigned* rout = xbase + (size_t)(s & 1) * ly * GXW;
         const R* cs = cbase + (int64_t)s * g.Tp * 64;
         const int64_t rows_left = (int64_t)g.nsteps_pad - (int64_t)s * g.Tp;
@@ -1470,7 +1477,7 @@ void k_sweep_pipe(const PipeArgs<R> a) {
                         for (int n = 2; n <= N; ++n) Qin[n] = (R)0;
                         Ein = 0;
                     } else {
-                        sk_edge_read<R, N>((SkLds<unsigned>)stage + u * GXW, Qin0, Qin1, Qin, Ein);
+                        sk_edge_read<R, N>((SkLds<sk_word>)stage + u * GXW, Qin0, Qin1, Qin, Ein);
                     }
                 }
                 if (sk_wave_any(E != Ein)) {
@@ -1532,11 +1539,10 @@ void k_sweep_pipe(const PipeArgs<R> a) {
                     } else {
                         unsigned* rec = rout + (int64_t)j * GXW;
                         unsigned wd[NW];
-                        *reinterpret_cast<double*>(wd) = Qo0;
-                        *reinterpret_cast<double*>(wd + 2) = Qo1;
+                        sk_put_words(wd, Qo0);
+                        sk_put_words(wd + 2, Qo1);
 #pragma unroll
-                        for (int n = 2; n <= N; ++n)
-                            *reinterpret_cast<R*>(wd + 4 + (n - 2) * (ES / 4)) = Qo[n];
+                        for (int n = 2; n <= N; ++n) sk_put_words(wd + 4 + (n - 2) * (ES / 4), Qo[n]);
                         wd[NW - 1] = (unsigned)E;
                         sk_store_record_coherent<NW>(rec, wd);
                     }
@@ -1589,7 +1595,7 @@ void k_sweep_pipe(const PipeArgs<R> a) {
                     for (int e0 = 0; e0 < 8 * QR; e0 += 64) {
                         const int e = e0 + rh, m = e / QR, w = e - m * QR, jc = t0 + m - 63;
                         if (e < 8 * QR && jc >= 0 && jc < ly) {
-                            const SkLds<unsigned> rec = ost + m * GXW;
+                            const SkLds<sk_word> rec = ost + m * GXW;
                             const int64_t o = (int64_t)(s + 1) * ly + jc;
                             if (w <= N) {
                                 R v;
@@ -1697,13 +1703,13 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     constexpr int ES = (int)sizeof(R), GXW = sk_gx_words(N, ES);
     const bool gx = GX && g.ly > a.gx_cols;  // wave-uniform
     extern __shared__ __align__(16) unsigned char sk_smem[];
-    unsigned* stage = reinterpret_cast<unsigned*>(sk_smem);  // [8][GXW]
+    sk_word* stage = reinterpret_cast<sk_word*>(sk_smem);  // [8][GXW]
     // boundary edges lane 0 replays at steps 1..S-1 of the current segment
     // (LDS-typed pointers: 32-bit address arithmetic)
-    SkLds<unsigned> qst = (SkLds<unsigned>)(sk_smem + sk_gx_stage_bytes(N, ES));
+    SkLds<sk_word> qst = (SkLds<sk_word>)(sk_smem + sk_gx_stage_bytes(N, ES));
     SkLds<R> llds = (SkLds<R>)(sk_smem + sk_gx_stage_bytes(N, ES) + sk_adj_qst_bytes(N, ES));
     SkLds<int> ltag = (SkLds<int>)(llds + g.ly * (N + 1));
-    unsigned* xg = a.xb + pd.xb_off;
+    sk_word* xg = a.xb + pd.xb_off;
     unsigned xr[(8 * GXW + 63) / 64];
 #pragma unroll
     for (int h = 0; h < (8 * GXW + 63) / 64; ++h) xr[h] = 0u;
@@ -1770,7 +1776,7 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
             if (s0 >= 1 && s0 < g.nstrips && j0 < g.ly && s0 * 64 < g.lx) {
                 const int64_t o = (int64_t)s0 * g.ly + j0;
                 if (w < (N + 1) * (ES / 4))
-                    pfq = reinterpret_cast<const unsigned*>(a.qb + pd.qb_off + o * (N + 1))[w];
+                    pfq = reinterpret_cast<const sk_word*>(a.qb + pd.qb_off + o * (N + 1))[w];
                 else if (w == QW - 1)
                     pfq = (unsigned)a.qe[pd.qe_off + o];
             }
@@ -1826,7 +1832,7 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
                     for (int n = 0; n <= N; ++n) Qin[n] = n == 0 ? (R)1 : (R)0;
                     Ein = 0;
                 } else if (PF) {
-                    const SkLds<unsigned> q = qst + (u - 1) * QW;
+                    const SkLds<sk_word> q = qst + (u - 1) * QW;
 #pragma unroll
                     for (int n = 0; n <= N; ++n) Qin[n] = ((SkLds<R>)q)[n];
                     Ein = (int)q[QW - 1];
@@ -1884,7 +1890,7 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
         }
         if (r == 63 && (FAST ? (unsigned)s63 < (unsigned)(g.nstrips - 1) : live && !last_row)) {
             if (gx) {
-                const unsigned* rec = stage + (tau & 7) * GXW;
+                const sk_word* rec = stage + (tau & 7) * GXW;
 #pragma unroll
                 for (int n = 0; n <= N; ++n)
                     lq_recv[n] = *reinterpret_cast<const R*>(rec + n * (ES / 4));
@@ -1948,7 +1954,7 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
         if (r == 0 && (FAST ? (unsigned)(sS - 1) < (unsigned)(g.nstrips - 1) : live && ss > 0)) {
             const int jw = FAST ? tT + u : jj;
             if (gx) {
-                unsigned* rec = xg + (int64_t)jw * GXW;
+                sk_word* rec = xg + (int64_t)jw * GXW;
 #pragma unroll
                 for (int n = 0; n <= N; ++n) *reinterpret_cast<R*>(rec + n * (ES / 4)) = lqs[n];
                 rec[(N + 1) * (ES / 4)] = (unsigned)Ec;
@@ -2251,7 +2257,7 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
     constexpr int TR = TMAX > 0 ? SkTailReg<R>::value : 0;
     constexpr int XR = (8 * GXW + 63) / 64, M = N + TR, RW = (N + 1) * (ES / 4) + 1;
     extern __shared__ __align__(16) unsigned char sk_smem[];
-    unsigned* stage = reinterpret_cast<unsigned*>(sk_smem);  // [8][GXW]
+    sk_word* stage = reinterpret_cast<sk_word*>(sk_smem);  // [8][GXW]
     R* dlds = reinterpret_cast<R*>(sk_smem + sk_gx_stage_bytes(N, ES)) + r;  // [2][S][M][64], this lane's slot
     auto DPu = [&](int u) { return dlds + (0 * S + u) * M * 64; };
     auto DQu = [&](int u) { return dlds + (1 * S + u) * M * 64; };
@@ -2261,9 +2267,9 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
     constexpr bool PF = ES == 4;
     constexpr int QW = sk_adj_qst_words(N, ES);
     static_assert(!PF || (S - 1) * QW <= 64, "staged boundary edges exceed one word per lane");
-    const SkLds<unsigned> qst =
-        (SkLds<unsigned>)(sk_smem + sk_gx_stage_bytes(N, ES) + 2 * S * M * 64 * ES);  // [S-1][QW]
-    const SkLds<unsigned> ost = qst + sk_adj_qst_bytes(N, ES) / 4;                      // [8][GXW]
+    const SkLds<sk_word> qst =
+        (SkLds<sk_word>)(sk_smem + sk_gx_stage_bytes(N, ES) + 2 * S * M * 64 * ES);  // [S-1][QW]
+    const SkLds<sk_word> ost = qst + sk_adj_qst_bytes(N, ES) / 4;                      // [8][GXW]
     for (int64_t q = blockIdx.x; q < a.njobs; q += gridDim.x) {
         const int2 jb = a.jobs[q];
         const SkPairDesc pd = a.desc[jb.x];
@@ -2274,7 +2280,7 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
         const int i = s * 64 + r;
         const bool rowok = i < g.lx;
         const bool has_next = s + 1 < g.nstrips;  // lane 63 receives from strip s+1
-        const unsigned* rin = a.xb + pd.xb_off + (size_t)((s + 1) & 1) * ly * GXW;
+        const sk_word* rin = a.xb + pd.xb_off + (size_t)((s + 1) & 1) * ly * GXW;
         unsigned* rout = a.xb + pd.xb_off + (size_t)(s & 1) * ly * GXW;
         int* prog = a.progress + pd.pg_off;
         const R* cs = a.cskew + pd.c_off + (int64_t)s * g.Tp * 64;
@@ -2356,7 +2362,7 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                         for (int n = 0; n <= N; ++n) Qin[n] = n == 0 ? (R)1 : (R)0;
                         Ein = 0;
                     } else if (PF) {
-                        const SkLds<unsigned> qq = qst + (u - 1) * QW;
+                        const SkLds<sk_word> qq = qst + (u - 1) * QW;
 #pragma unroll
                         for (int n = 0; n <= N; ++n) Qin[n] = ((SkLds<R>)qq)[n];
                         Ein = (int)qq[QW - 1];
@@ -2390,7 +2396,7 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
             // (FAST: lane 63 of the last strip keeps its own exponent for its zeros)
             int El_recv = FAST ? lane_from_next_or(Els, El) : lane_from_next(Els);
             if (r == 63 && (FAST ? has_next : live && !last_row)) {  // from strip s+1's lane 0
-                const unsigned* rec = stage + (t & 7) * GXW;
+                const sk_word* rec = stage + (t & 7) * GXW;
 #pragma unroll
                 for (int n = 0; n <= N; ++n) lq_recv[n] = *reinterpret_cast<const R*>(rec + n * (ES / 4));
                 El_recv = (int)rec[(N + 1) * (ES / 4)];
@@ -2443,14 +2449,14 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
             Els = Ec;
             if (live && r == 0 && s > 0) {  // to strip s-1's lane 63
                 if (PF) {  // (leaves with the block)
-                    const SkLds<unsigned> rec = ost + (t & 7) * GXW;
+                    const SkLds<sk_word> rec = ost + (t & 7) * GXW;
 #pragma unroll
                     for (int n = 0; n <= N; ++n) *(SkLds<R>)(rec + n * (ES / 4)) = lqs[n];
                     rec[RW - 1] = (unsigned)Ec;
                 } else {
                     unsigned wd[RW];
 #pragma unroll
-                    for (int n = 0; n <= N; ++n) *reinterpret_cast<R*>(wd + n * (ES / 4)) = lqs[n];
+                    for (int n = 0; n <= N; ++n) sk_put_words(wd + n * (ES / 4), lqs[n]);
                     wd[RW - 1] = (unsigned)Ec;
                     unsigned* rec = rout + (int64_t)jj * GXW;
 #pragma unroll
@@ -2488,7 +2494,7 @@ __device__ __forceinline__ void sk_adjoint_pipe_body(const AdjPipeArgs<R>& a) {
                 if (j < ly) {
                     const int64_t o = (int64_t)s * ly + j;
                     if (w < (N + 1) * (ES / 4))
-                        v = reinterpret_cast<const unsigned*>(a.qb + pd.qb_off + o * (N + 1))[w];
+                        v = reinterpret_cast<const sk_word*>(a.qb + pd.qb_off + o * (N + 1))[w];
                     else if (w == QW - 1)
                         v = (unsigned)a.qe[pd.qe_off + o];
                 }
