@@ -2150,8 +2150,10 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
         tau0 -= S;
         for (tT -= S; tT < 0 && sS > 0; tT += g.Tp) --sS;
     };
-    // (FP64 kernels of one wave per SIMD, bound by their general registers,
-    // gain 2-4% from fast segments at most and go without them)
+    // (FP64 kernels of one wave per SIMD go without fast segments: they gain 2-4%
+    // at most, and a second kind of segment takes them to 350-410 registers,
+    // where the compiler parked live registers in AGPRs under a partial EXEC
+    // mask: the order 12 exchange adjoint so built gave wrong gradients)
     constexpr bool FASTK = ES == 4 || sk_adj_two_waves<R, N, TMAX, GX>();
     auto fast = [&]() SK_INLINE {  // wave-uniform
         return fastp && kk >= 0 && tT + S < Tf;
