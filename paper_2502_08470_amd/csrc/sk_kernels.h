@@ -1366,7 +1366,7 @@ __device__ __forceinline__ bool sk_wait_count(const int* prog, int need, int& se
 
 template <typename R, int N, int TMAX, bool CKPT, int S>
 __global__ __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 1 : CKPT && N >= 5 ? 3 : TMAX == 0 || N <= 6 ? 4 : 3, 8)))
+__attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? (N > 9 ? 2 : 1) : CKPT && N >= 5 ? 3 : TMAX == 0 || N <= 6 ? 4 : 3, 8)))
 void k_sweep_pipe(const PipeArgs<R> a) {
     SkTabArg<R>& tab = sk_kernarg<PipeArgs<R>>().tab;
     const int r = threadIdx.x;
@@ -1378,7 +1378,11 @@ void k_sweep_pipe(const PipeArgs<R> a) {
     // slot by all lanes at the block's end (before it is published)
     const SkLds<sk_word> ost = (SkLds<sk_word>)(sk_smem + sk_gx_stage_bytes(N, ES));  // [8][GXW]
     constexpr int NW = 4 + (N - 1) * (ES / 4) + 1;  // words of a record
-    constexpr int HU = TMAX == 0 ? 8 : 4;  // steps unrolled together (as in k_sweep)
+    // FP64 interpolation of the highest orders: a second kind of block would
+    // cost the second wave per SIMD (1024 pairs of 100 x 300 cells, N = 10: 1.07
+    // ms with it, 0.95 without)
+    constexpr bool FASTK = ES == 4 || TMAX == 0 || N <= 9;
+    constexpr int HU = TMAX == 0 || !FASTK ? 8 : 4;  // steps unrolled together (as in k_sweep)
     for (int64_t q = blockIdx.x; q < a.njobs; q += gridDim.x) {
         // the job: strip s of a pair with geometry g and arrays at these bases
         const int2 jb = a.jobs[q];
@@ -1574,8 +1578,13 @@ void k_sweep_pipe(const PipeArgs<R> a) {
                     for (int u = 0; u < HU; ++u) step(h + u, u, cg[u], fastc);
                 }
             };
-            if (t0 >= 64 && t0 + 8 < ly) steps(std::true_type{});
-            else steps(std::false_type{});
+            bool fast = false;
+            if constexpr (FASTK) fast = t0 >= 64 && t0 + 8 < ly;
+            if (fast) {
+                if constexpr (FASTK) steps(std::true_type{});
+            } else {
+                steps(std::false_type{});
+            }
             // CKPT: lane 63's records of this block (columns t0 + m - 63
             // that exist) to strip s+1's slot and to the adjoint's copy of
             // the boundary edges, in one pass of all lanes (without CKPT lane
