@@ -1699,7 +1699,17 @@ constexpr bool sk_adj_two_waves() {
                           : (TMAX == 0 && N <= 6 && !GX);
 }
 
-template <typename R, int N, int TMAX, int S, bool GX>
+// Where the prefetched state costs a wave per SIMD that launches of many pairs
+// would fill (FP64 approximation, N = 4: 200 registers with it, 158 without),
+// those launches take a third entry point without it: 2304 pairs of 256 x 256
+// cells 2.45 -> 2.07 ms; 64 pairs of 300 x 200 cells 0.79 ms with it, 0.97
+// without, and 4096 pairs of 1000 x 20 cells, general segments throughout, 4.8
+// and 5.5.
+template <typename R, int N, int TMAX, bool GX>
+constexpr bool sk_adj_three_waves() { return sizeof(R) == 8 && TMAX == 0 && N == 4 && !GX; }
+#define SK_ADJ_TWO_WAVES_PAIRS 2048  // two waves on each of 1024 SIMDs
+
+template <typename R, int N, int TMAX, int S, bool GX, bool AHEAD = true>
 __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     SkTabArg<R>& tab = sk_kernarg<AdjArgs<R>>().tab;
     const int r = threadIdx.x;
@@ -1758,7 +1768,7 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     // state would cost a wave per SIMD; 4096 pairs of 1000 x 20 cells, N = 7:
     // 7.4 ms prefetched, 6.0 not)
     constexpr bool PF64 = N <= 8 && (TMAX > 0 || (sk_adj_two_waves<R, N, TMAX, GX>() ? N <= 5 : N >= 5 && N != 7));
-    constexpr bool PF = S >= 4 || (ES == 8 && PF64);
+    constexpr bool PF = AHEAD && (S >= 4 || (ES == 8 && PF64));
     constexpr int QW = sk_adj_qst_words(N, ES), TWL = (S - 1) * QW;
     static_assert(!PF || (S <= 4 && TWL < 64), "staged boundary edges exceed one word per lane");
     R pfP[N + 1], pfQ[N + 1], pfc[S];
@@ -2200,6 +2210,12 @@ template <typename R, int N, int TMAX, int S, bool GX>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void k_adjoint_w2(const AdjArgs<R> a) {
     sk_adjoint_body<R, N, TMAX, S, GX>(a);
+}
+
+template <typename R, int N, int TMAX, int S, bool GX>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8)))
+void k_adjoint_w3(const AdjArgs<R> a) {
+    sk_adjoint_body<R, N, TMAX, S, GX, false>(a);
 }
 
 template <typename R, int N, int TMAX, int S, bool GX>

@@ -302,6 +302,13 @@ hipError_t SkLaunch<R>::adjoint_pipe(const AdjPipeArgs<R>& a, int N, bool interp
 template <typename R, int N, int TMAX, bool GX, int S>
 static hipError_t sk_adj_gs(const AdjArgs<R>& a, int64_t npairs, int ring, hipStream_t st) {
     size_t lds = SkLaunch<R>::adjoint_lds(N, ring);
+    if constexpr (sk_adj_three_waves<R, N, TMAX, GX>()) {
+        if (npairs > SK_ADJ_TWO_WAVES_PAIRS && ring > SK_LANES) {
+            hipLaunchKernelGGL((k_adjoint_w3<R, N, TMAX, S, GX>), dim3((unsigned)npairs), dim3(64), lds, st, a);
+            SK_CHECK_LAUNCH();
+            return hipSuccess;
+        }
+    }
     if constexpr (sk_adj_two_waves<R, N, TMAX, GX>())
         hipLaunchKernelGGL((k_adjoint_w2<R, N, TMAX, S, GX>), dim3((unsigned)npairs), dim3(64), lds,
                            st, a);
