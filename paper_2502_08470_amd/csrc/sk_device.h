@@ -436,7 +436,11 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
             }
         }
     }
-    if (__builtin_expect(full, SMALL == SK_SMALL_OFF)) {
+    // (the tail's rows stand in the way where the tail is decided: no side is
+    // laid out as the rare one there.  64 FP32 pairs of 700 x 90 cells that all
+    // have a tail, N = 6: checkpoint sweep 1.44 -> 1.19 ms)
+    constexpr bool EVEN = TMAX > 0 && !FIXT;
+    if (EVEN ? full : __builtin_expect(full, SMALL == SK_SMALL_OFF)) {
 #pragma unroll
         for (int m = M0 + 1; m <= MU; ++m) power(m);
 #pragma unroll
@@ -452,7 +456,7 @@ __device__ __forceinline__ void sk_cell_fwd(const R (&P)[N + 1], const R (&Q)[N 
 #pragma unroll
         for (int m = 1; m <= (M0 < N ? M0 : N); ++m) Wout[m - 1] = w[m];
     }
-    if (TMAX > 0 && __builtin_expect(full, SMALL == SK_SMALL_OFF)) {
+    if (TMAX > 0 && (EVEN ? full : __builtin_expect(full, SMALL == SK_SMALL_OFF))) {
         const R scale = (R)SkEps<R>::value * (R)(fabs(Po0) + fabs(Qo0));
         const R ac = sk_abs(c);
         R t0p = (R)0, t0q = (R)0, t1p = (R)0, t1q = (R)0;  // tail into rows 0, 1

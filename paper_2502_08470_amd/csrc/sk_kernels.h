@@ -962,8 +962,10 @@ void k_sweep(const SweepArgs<R> a) {
     // steps unrolled together: few where a pair would run through cold
     // instructions for as long as it computes (interpolation; general blocks,
     // of which most pairs have one: 408 pairs of 49 x 40 cells, FP32 order 4,
-    // sweep 106 us with 8 steps of both kinds, 96 with 4)
-    constexpr int HF = TMAX == 0 ? 8 : 4, HG = 4;
+    // sweep 106 us with 8 steps of both kinds, 96 with 4).  The exchange's pairs
+    // are long: 8 (16 FP64 pairs of 2048 x 2048 cells, interpolation N = 4: 94.5
+    // -> 81 ms)
+    constexpr int HF = TMAX == 0 || GX ? 8 : 4, HG = 4;
     unsigned tword = 0u;  // tail lengths of the current checkpoint segment
     // FAST blocks: pairs whose strips follow each other without idle columns
     // (Tp = ly, and more than 64 columns, so that the entry lane 0 reads one
