@@ -1109,6 +1109,11 @@ void k_sweep(const SweepArgs<R> a) {
         const int jc = FAST ? jS : j;  // lane 63's column
         if (r == 63 && (FAST ? (unsigned)(tau - 63) < handed : live && s + 1 < g.nstrips)) {
             if (gx) {
+                // (the checkpoint copy leaves once per block, from LDS; written
+                // first, or the compiler joins this write and the ring's behind
+                // the branch, in 8-byte stores: 16 FP32 pairs of 2048 x 2048
+                // cells, N = 3, 24.1 ms so and 26.2 joined)
+                if (CKPT) sk_edge_write<R, N>(ost + u * GXW, Qo0, Qo1, Qo, E);
                 // the record in 16-byte stores (records are 16-byte
                 // aligned, GXW words each)
                 constexpr int NW = 4 + (N - 1) * (ES / 4) + 1, NQ = (NW + 3) / 4;
@@ -1133,8 +1138,6 @@ void k_sweep(const SweepArgs<R> a) {
 #pragma unroll
                 for (int k = 0; k < NQ; ++k)
                     rec[k] = make_uint4(wd[4 * k], wd[4 * k + 1], wd[4 * k + 2], wd[4 * k + 3]);
-                // (the checkpoint copy leaves once per block, from LDS)
-                if (CKPT) sk_edge_write<R, N>(ost + u * GXW, Qo0, Qo1, Qo, E);
             } else {
                 // (the checkpoint copy of ring entries leaves once per block)
                 sk_edge_write<R, N>(ring + __mul24(jc, RW), Qo0, Qo1, Qo, E);
