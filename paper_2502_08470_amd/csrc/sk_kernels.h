@@ -1458,12 +1458,21 @@ void k_sweep_pipe(const PipeArgs<R> a) {
                 v[u] = cs[(row + u < rows_left ? (int64_t)(row + u) : rows_left - 1) * 64 + r];
         };
         load_c(cb, 0);
+        // Steps at which the approximation's cells of small |c| may take their
+        // shorter rows: those of the batched sweep, which decides by the same row
+        // of constants (a strip's first steps hold the last cells of the strip
+        // above too), so that both algorithms give the same values.  (The
+        // interpolation's tails are decided per wave in any case.)
+        const int batched_end = !(g.nstrips == 1 || (g.Tp == ly && ly > 64)) ? 0
+            : g.nstrips == 1 || g.nsteps < g.nstrips * g.Tp ? g.nsteps & ~7 : (g.nstrips * g.Tp) & ~7;
+        const int small0 = (g.nstrips == 1 ? 0 : 64) - s * g.Tp, small1 = batched_end - s * g.Tp;
         // Step u of the block (um = u modulo HU).  FAST: a block in which every lane is inside the
         // strip, past its first column and before its last (see k_sweep).
         auto step = [&](int u, int um, R cu, auto fastc) SK_INLINE {
             constexpr bool FAST = decltype(fastc)::value;
-            constexpr int SMALL = FAST && sk_small_path<R, N>() ? SK_SMALL_ASK : SK_SMALL_OFF;
+            constexpr int SMALL = (FAST || TMAX == 0) && sk_small_path<R, N>() ? SK_SMALL_ASK : SK_SMALL_OFF;
             const int t = t0 + u, j = t - r;
+            const R small_c = TMAX > 0 || (t >= small0 && t < small1) ? (R)SK_SMALL_C : (R)-1;
             R Qin[N + 1];
 #pragma unroll
             for (int n = 2; n <= N; ++n) Qin[n] = lane_from_prev(Qs[n]);
@@ -1522,7 +1531,7 @@ void k_sweep_pipe(const PipeArgs<R> a) {
             int Tc = 0;
             sk_cell_fwd<R, N, TMAX, false, true, false, 1, SMALL>(
                 P, Qin, P0, P1, Qin0, Qin1, cu, live, tab, Po, Qo, Po0, Po1, Qo0, Qo1, nullptr,
-                nullptr, (CKPT && TMAX > 0) ? &Tc : nullptr);
+                nullptr, (CKPT && TMAX > 0) ? &Tc : nullptr, 0, nullptr, small_c);
             if (CKPT && TMAX > 0) {
                 // the adjoint's replay folds the same tail rows
                 tword |= (unsigned)Tc << (8 * (um % S));
