@@ -105,6 +105,8 @@ template <typename R>
 hipError_t SkLaunch<R>::gram_band(const GramArgs<R>& a0, int max_strips, int max_rows,
                                   int64_t npairs, hipStream_t st) {
     if (npairs <= 0 || max_strips <= 0 || max_rows <= 0) return hipSuccess;
+    // (the kernel's registers hold 48 split coordinates, or 16 values a thread)
+    if (a0.dpad > (a0.split ? 48 : 64)) return hipErrorInvalidValue;
     // split each strip's rows so that the launch has about 2048 workgroups,
     // segments of at least 256 rows (a multiple of 64)
     const int64_t wgs = npairs * (int64_t)max_strips;
