@@ -437,28 +437,39 @@ def _state_budget(device) -> int:
 # The strip pipeline pays while the batched algorithm, which gives every pair
 # one wave, leaves most of the GPU's 256 CUs x 4 SIMDs idle (an 8 x 8 Gram of
 # 2049-point paths in R^16: backward 173 ms batched, 17 ms pipelined).  Times
-# of both, in units of one batched pair's strips x columns steps, P = pairs per
-# SIMD (fitted to backwards of 4 to 2048 pairs, 2 to 16 strips, 96 to 1500
-# columns; the forward's lines lie close by):
-#   batched: waves of one SIMD share it well in FP32, 1 + P / 4; in FP64 the
-#     adjoint keeps one wave per SIMD, 1 + 0.55 P^2 up to P = 1, then 1.45 P;
-#   pipelined: its depth, a strip starting about 150 columns behind the one
-#     above it, or once the GPU is full 0.6 of the depth and the strips' own
-#     steps (columns + 63 of skew each), which FP64 runs at half FP32's rate.
-# Forward / backward in ms: 384 FP32 pairs of order 6, 160 x 130 cells 0.25 /
-# 0.68 batched, 0.30 / 0.81 pipelined; 256 x 256 cells 0.60 / 1.62 and 0.46 /
-# 1.23, of 2048 pairs 0.73 / 2.23 and 0.81 / 2.85.  Backward, 600 pairs of
-# 120 x 1500 cells: FP32 3.59 batched, 2.63 pipelined, FP64 5.66 and 4.71; 1600
-# FP64 pairs of 300 x 100 1.83 and 2.73; training step of 1073 FP64 pairs of
-# 150 x 202 cells 2.28 and 2.65.  Calls of fewer than 64 pairs always take the
-# pipeline (96 x 96 cells: 0.20 / 0.50, batched 0.14 / 0.35).
+# of both, in units of one batched pair's strips x columns steps, with P pairs
+# per SIMD, fitted to approximation calls of orders 4, 6 and 8, 64 to 2040 pairs
+# of 66 x 66 to 1000 x 1000 cells:
+#   batched: max(1 + a P^e, r P + r0), waves sharing a SIMD and then queueing;
+#   pipelined: max(k D, f D + g P (columns + 63) / columns) with its depth D, a
+#     strip starting `lag` columns behind the one above it, and once the GPU is
+#     full a part of the depth and the strips' own steps.
+# The precision is the sweep's.  Backwards in FP64 have their own line from order
+# 7 on, where the batched adjoint keeps one wave per SIMD.  With these lines the
+# slower algorithm is taken on 2% of the shapes, by 21% at most (1700 FP64 pairs
+# of 66 x 500 cells, order 4, backward: 4.1 ms pipelined, 3.2 batched; 2040 FP32
+# pairs of 500 x 500, order 8: 14.5 ms batched, 11.9 pipelined on a line that
+# forwards and backwards shared).
+# Calls of fewer than 64 pairs take the pipeline whatever their shape, as they
+# always did; short ones are slower on it (16 FP32 pairs of 66 x 66 cells, order
+# 4: backward 0.34 ms pipelined, 0.18 batched), which tune_gram finds.
 PIPELINE_MAX_PAIRS = 2048
 PIPELINE_FEW_PAIRS = 64
+#              a     e  r      r0    lag  k     f     g
+_ALGO_LINES = {
+    "f32 forward": (0.45, 1, 0.63, 0.43, 200, 1.07, 0.59, 0.72),
+    "f32 backward": (0.25, 1, 0.885, 0.23, 151, 1.18, 0.31, 0.81),
+    "f64 forward": (0.17, 2, 0.74, 0.04, 193, 0.91, 0.76, 0.49),
+    "f64 backward": (0.25, 2, 1.38, 0.44, 172, 1.13, 0.28, 1.37),
+    "f64 backward 7": (0.84, 1, 1.63, 0.36, 178, 0.91, 0.82, 1.04),
+}
 
 
-def gram_algo(X: torch.Tensor, Y: torch.Tensor, scheme: str = "approx") -> str:
+def gram_algo(X: torch.Tensor, Y: torch.Tensor, scheme: str = "approx", order: int = 4,
+              sweep: str = "native", backward: bool = True) -> str:
     """"pipeline" for polynomial-scheme Gram calls of few pairs whose paths
-    span several strips, else "batched"."""
+    span several strips, else "batched" (``sweep`` as in gram; ``backward``:
+    the call's state is kept for, or followed by, a backward)."""
     if scheme in ("fd", "fd2"):
         return "batched"
     strips = (X.shape[1] - 2) // 64 + 1 if X.shape[1] > 1 else 0
@@ -467,11 +478,13 @@ def gram_algo(X: torch.Tensor, Y: torch.Tensor, scheme: str = "approx") -> str:
         return "batched"
     if pairs < PIPELINE_FEW_PAIRS:
         return "pipeline"
-    f64 = X.dtype == torch.float64
+    f64 = X.dtype == torch.float64 or sweep == "f64"
+    line = ("f64 " if f64 else "f32 ") + ("backward" if backward else "forward")
+    a, e, r, r0, lag, k, f, g = _ALGO_LINES[line + " 7" if f64 and backward and order >= 7 else line]
     per_simd = pairs / 1024
-    batched = 1 + 0.25 * per_simd if not f64 else max(1 + 0.55 * min(per_simd, 1) ** 2, 1.45 * per_simd + 0.1)
-    depth = (cols + 63 + 150 * (strips - 1)) / (strips * cols)
-    pipelined = max(depth, 0.6 * depth + (1.06 if f64 else 0.58) * per_simd * (cols + 63) / cols)
+    batched = max(1 + a * per_simd ** e, r * per_simd + r0)
+    depth = (cols + 63 + lag * (strips - 1)) / (strips * cols)
+    pipelined = max(k * depth, f * depth + g * per_simd * (cols + 63) / cols)
     return "pipeline" if pipelined < batched else "batched"
 
 
@@ -561,8 +574,8 @@ class SigKernelGram(torch.autograd.Function):
         ctx.scheme, ctx.order, ctx.gram_mode, ctx.dyadic = scheme, order, gram_mode, dyadic
         ctx.sweep = sweep
         ctx.ckpt = 0
+        bwd = scheme not in ("fd", "fd2") and (X.requires_grad or Y.requires_grad)
         if algo is None:
-            bwd = scheme not in ("fd", "fd2") and (X.requires_grad or Y.requires_grad)
             t = gram_tuned(X, Y, scheme, order, gram_mode, dyadic, sweep, backward=bwd,
                            symmetric=X is Y)
             if t is None and tune and X.shape[0] * Y.shape[0] > 0:
@@ -570,7 +583,7 @@ class SigKernelGram(torch.autograd.Function):
                               backward=bwd, symmetric=X is Y)
             if t is not None:
                 algo, ctx.ckpt = t["algo"], t["ckpt"]
-        ctx.algo = algo or gram_algo(X, Y, scheme)
+        ctx.algo = algo or gram_algo(X, Y, scheme, order, sweep, bwd)
         # the same tensor on both sides: one gradient with both contributions
         ctx.symmetric = X is Y
         ctx.state = None
