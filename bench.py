@@ -14,7 +14,12 @@ Inputs are resident on the GPU before timing.  Reported:
 * gram_entries_per_s: Gram entries per second (fwd+bwd).
 * mape: mean |K_gpu / K_oracle - 1| on the 16 x 16 block X[0:16] x Y[0:16]
   against the FP64 oracle.
-* roofline: dominant kernel, algorithmic FLOPs / its HIP-event time.
+* roofline: dominant kernel, the FLOPs of the rows its cells take / its
+  HIP-event time (steps whose cells all have |c| <= 2^-6 take short rows: their
+  share of the cells is counted on a sample of pairs; all_rows_flops_per_cell is the count of
+  a cell that takes every row).
+* large_cells: the same step on the points times 4, whose cells (|c| 16 times
+  as large) take every row and a tail.
 * cpu_baseline: the FP64 C oracle on the 48 x 64 block X[0:48] x Y[0:64]
   (about 10-20 s on 16 host cores), all host threads OMP_NUM_THREADS allows;
   its `single_core` entry times one thread on the 4 x 8 block, and `host`
@@ -198,6 +203,29 @@ def fwd_cell_flops(N: int, T: int, deciding: bool = False) -> float:
     return 2.0 * fma + 3 * N
 
 
+def small_cell_flops(N: int) -> float:
+    """FLOPs of one forward cell on the rows of small |c|, per edge: Toeplitz
+    rows from the weights w_1..w_3 (3N - 3 FMA), Hankel rows up to r = 3 (4N and
+    4 to combine) and the w_4 term; and 11 multiplies for the weights and w_4."""
+    return 2.0 * 2 * (7 * N + 2) + 11
+
+
+def small_cell_share(C, limit: float = 2.0 ** -6) -> float:
+    """Share of the cells in steps of the batched sweep at which all 64 lanes have
+    |c| <= limit (constants C: pairs x lx x ly, more than 64 columns; lane r of
+    step t holds column t - r of its strip, or of the strip before)."""
+    P, lx, ly = C.shape
+    strips = (lx + 63) // 64
+    top = np.zeros((P, strips * ly + 63), dtype=np.float64)
+    cells = np.zeros(strips * ly + 63)
+    for i in range(lx):
+        at = (i // 64) * ly + i % 64
+        np.maximum(top[:, at:at + ly], np.abs(C[:, i]), out=top[:, at:at + ly])
+        cells[at:at + ly] += 1
+    blocks = slice(64, strips * ly // 8 * 8)  # the first and the last steps are general
+    return float(((top[:, blocks] <= limit) * cells[blocks]).sum() / (P * lx * ly))
+
+
 def accuracy_study() -> int:
     """MAPE (fraction) of every scheme against the converged kernel on 8 x 8
     Grams of 2-d Brownian motions on [0, 1] with 10, 50 and 200 steps, the
@@ -272,12 +300,11 @@ def long_pair_study(steps: int = 16384) -> int:
             kern = {name: _lib.profile_read(name)[0] / reps
                     for name in ("gram", "sweep", "sweep_pipe")}
             _lib.profile_enable(False)
-            fl = fwd_cell_flops(order, 0, deciding=scheme == "interp")
+            fl = fwd_cell_flops(order, 0, deciding=scheme == "interp")  # every row: small cells take fewer
             rows.append({"scheme": scheme, "order": order, "algo": algo, "ms": ms,
                          "kernel_ms": {n: v for n, v in kern.items() if v > 0},
                          "cells_per_s": cells / (ms * 1e-3),
-                         "tflops": fl * cells / (ms * 1e-3) / 1e12,
-                         "frac_of_fp32_peak": fl * cells / (ms * 1e-3) / PEAK_FP32_VALU,
+                         "all_rows_tflops": fl * cells / (ms * 1e-3) / 1e12,
                          "k": float(k.cpu()[0, 0])})
             print(f"[bench] long pair {scheme} {order} {algo}: {ms:.2f} ms", file=sys.stderr,
                   flush=True)
@@ -668,8 +695,13 @@ def main(argv=None) -> int:
     # adjoint replays the forward with the recorded T (no deciding row) and
     # applies the transposed map: 2 forwards without the deciding row (the
     # dL/dc terms are not counted)
-    fl_fwd = fwd_cell_flops(ORDER, 0, deciding=True)
-    fl_adj = 2.0 * fwd_cell_flops(ORDER, 0)
+    small = small_cell_share(np.einsum("aik,bjk->abij", np.diff(X[:8], axis=1), np.diff(Y[:8], axis=1))
+                             .reshape(64, STEPS, STEPS))
+    def mixed(all_rows, short_rows):
+        return small * short_rows + (1.0 - small) * all_rows
+    fl_all = {"sweep": fwd_cell_flops(ORDER, 0, deciding=True), "adjoint": 2.0 * fwd_cell_flops(ORDER, 0)}
+    fl_fwd = mixed(fl_all["sweep"], small_cell_flops(ORDER))
+    fl_adj = mixed(fl_all["adjoint"], 2.0 * small_cell_flops(ORDER))
     flops_per_cell = {"sweep": fl_fwd, "sweep_ckpt": fl_fwd, "adjoint": fl_adj,
                       "sweep_pipe": fl_fwd, "sweep_ckpt_pipe": fl_fwd, "adjoint_pipe": fl_adj,
                       "gram": 2.0 * DIM, "contract": 4.0 * DIM}
@@ -686,7 +718,9 @@ def main(argv=None) -> int:
                 "frac": achieved / PEAK_FP32_VALU,
                 "traffic": None if tr is None else tr["bytes"],
                 "traffic_unit": "bytes per launch (HBM fetch + write)",
-                "flops_per_cell": flops_per_cell[dom], "launch_ms": dom_ms / dom_n,
+                "flops_per_cell": flops_per_cell[dom], "small_cell_share": small,
+                "all_rows_flops_per_cell": fl_all["adjoint" if dom.startswith("adjoint") else "sweep"]
+                if dom not in ("gram", "contract") else flops_per_cell[dom], "launch_ms": dom_ms / dom_n,
                 "launches_per_step": dom_n / args.steps,
                 "kernel_ms_per_step": {k: ktimes[k][0] / args.steps for k in kernels}}
 
@@ -701,8 +735,21 @@ def main(argv=None) -> int:
                       "pairs": N_PATHS * N_PATHS, "cells_per_pair": STEPS * STEPS,
                       "gram_kernel": "k_gram_direct",
                       "schedule": tuned if tuned is not None else
-                      {"algo": sk.gram_algo(Xt, Yt, SCHEME), "ckpt": 4, "tuned": False}},
+                      {"algo": sk.gram_algo(Xt, Yt, SCHEME, ORDER), "ckpt": 4, "tuned": False}},
            "gram_entries_per_s": entries, "roofline": roofline}
+
+    # the same step where no cell is small
+    if not args.no_plain:
+        Xl, Yl = (4.0 * Xt.detach()).requires_grad_(True), (4.0 * Yt.detach()).requires_grad_(True)
+        for it in range(5):
+            if it == 2:
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+            Xl.grad = Yl.grad = None
+            sk.sig_gram(Xl, Yl, SCHEME, ORDER).sum().backward()
+        torch.cuda.synchronize()
+        out["large_cells"] = {"points_times": 4, "ms_per_step": (time.perf_counter() - t0) * 1e3 / 3}
+        del Xl, Yl
 
     # accuracy on the 16 x 16 block (and the larger CPU sample), CPU oracle
     from oracle import c_oracle as C
