@@ -976,9 +976,9 @@ void k_sweep(const SweepArgs<R> a) {
     // lanes enter a strip.  Lanes without a cell (before their first, after
     // their last, past the pair's last row) have c = 0 and compute values that
     // no cell reads.  Lane 0's edge of the next step is read from LDS one step
-    // ahead, and cells of small |c| take their shorter rows (SK_SMALL_C; where
-    // strips of several are all filled, as in the strip pipeline, whose values
-    // are the same to the last bit while no |c| is small).  The sweep is bound
+    // ahead, and cells of small |c| take their shorter rows (SK_SMALL_C; of
+    // several strips at the steps that all lanes have a cell in, and in the strip
+    // pipeline at the same steps).  The sweep is bound
     // by vector instructions: 128 x 128 FP32 pairs of 256 x 256 cells, N = 6:
     // 7.8 -> 3.9 ms, with checkpoints 7.9 -> 5.3; 64 FP64 pairs of 64 x 64, by
     // the depth of one wave, 51 -> 42 us.
@@ -1386,6 +1386,12 @@ void k_sweep_pipe(const PipeArgs<R> a) {
     // FP64 interpolation of the highest orders: a second kind of block would
     // cost the second wave per SIMD (1024 pairs of 100 x 300 cells, N = 10: 1.07
     // ms with it, 0.95 without)
+    // FP32 approximation without checkpoints: both kinds of blocks and rows take
+    // 128 registers, four waves per SIMD instead of five.  One pair of 16384 x
+    // 16384 cells, N = 8: 32.1 -> 22.3 ms, 16 of 2048 x 2048 4.0 -> 2.9; 4096
+    // pairs of 32 to 2048 points with no small cell, enough strips to fill the
+    // chip, 36.0 -> 38.6 (five waves with one kind of block: 36.6, and 27.6 and
+    // 3.4 for the other two).
     constexpr bool FASTK = ES == 4 || TMAX == 0 || N <= 9;
     constexpr int HU = TMAX == 0 || !FASTK ? 8 : 4;  // steps unrolled together (as in k_sweep)
     for (int64_t q = blockIdx.x; q < a.njobs; q += gridDim.x) {
@@ -1705,8 +1711,9 @@ struct AdjArgs {
 // Two entry points of the same body: where the register footprint allows it,
 // the compiler is asked to fit two waves per SIMD (the adjoint is latency
 // bound at one); elsewhere forcing it would spill to scratch.  The FP32
-// exchange variant for N = 8 (approximation) spills 6 registers at two waves
-// and is still faster (1024 x 1024 d = 32 Gram, 32 rows: 1021 -> 647 ms).
+// approximation for N = 8 spills 20 registers at two waves, 25 with the
+// exchange, and is still faster (1024 x 1024 d = 32 Gram, 32 rows, exchange, 6
+// spilled then: 1021 -> 647 ms).
 template <typename R, int N, int TMAX, bool GX>
 constexpr bool sk_adj_two_waves() {
     return sizeof(R) == 4 ? (GX ? TMAX == 0 : (TMAX == 0 || N <= 6))
@@ -1714,7 +1721,7 @@ constexpr bool sk_adj_two_waves() {
 }
 
 // Where the prefetched state costs a wave per SIMD that launches of many pairs
-// would fill (FP64 approximation, N = 4: 200 registers with it, 158 without),
+// would fill (FP64 approximation, N = 4: 200 registers with it, 164 without),
 // those launches take a third entry point without it: 2304 pairs of 256 x 256
 // cells 2.45 -> 2.07 ms; 64 pairs of 300 x 200 cells 0.79 ms with it, 0.97
 // without, and 4096 pairs of 1000 x 20 cells, general segments throughout, 4.8
@@ -1778,9 +1785,10 @@ __device__ __forceinline__ void sk_adjoint_body(const AdjArgs<R>& a) {
     // steps 1..S-1 (plus, in lane TWL, the tail-length word) once the
     // previous segment's replay no longer needs its own.  The boundary edges
     // go through LDS, so no load is waited for inside a segment.
-    // (FP64 approximation, N = 7 and the exchange at N <= 4: the prefetched
+    // (FP64 approximation, N = 6 and 7 and the exchange at N <= 4: the prefetched
     // state would cost a wave per SIMD; 4096 pairs of 1000 x 20 cells, N = 7:
-    // 7.4 ms prefetched, 6.0 not)
+    // 7.4 ms prefetched, 6.0 not.  At N = 8 it costs one too: 282 registers, 243
+    // without it.)
     constexpr bool PF64 = N <= 8 && (TMAX > 0 || (sk_adj_two_waves<R, N, TMAX, GX>() ? N <= 5 : N >= 5 && N != 7));
     constexpr bool PF = AHEAD && (S >= 4 || (ES == 8 && PF64));
     constexpr int QW = sk_adj_qst_words(N, ES), TWL = (S - 1) * QW;
